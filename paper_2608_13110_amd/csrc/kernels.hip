@@ -4,9 +4,10 @@
 //  k_resolve  per-batch choice of every update's matrix variant
 //  k_pass     one fused window of staircase updates over every tile of the
 //             boundary tensor (the hot loop); in place, HBM-streaming
-//  k_late     the folded late-phase contraction: the Alg. 2 join and the late
-//             layers, FP64 accumulation (k_late_mf: the same on FP64 matrix
-//             cores), and k_late_ops, the rest of the late program
+//  k_late_*   the folded late-phase contraction: the Alg. 2 join and the late
+//             layers, FP64 accumulation (k_late_mf on FP64 matrix cores,
+//             k_late_dot and k_late_out for narrow products), and k_late_ops,
+//             the rest of the late program
 //  k_logxeb   FP64 log-XEB reduction; samplers
 //
 // The kernels of the amplitude path are recorded as launches (Launch, see
@@ -820,10 +821,15 @@ void emulate_pass_host(const PassArgs& a, int R) {
 
 // ---------------------------------------------------------------------------
 // Late phase: out[b][r][c] = sum_kk in[b][r][kk] * J[var][kk][c] in FP64.
-// J folds, on the host, the early-region tensor Z_early (first launch), the
-// late layers' one- and two-qubit gates and the removal of the crossing
-// bonds between the fixed rows and the open band (Alg. 2).  Tiled 64 x 64
-// per block, K in steps of 16, 4 x 4 complex accumulators per thread.
+// J folds the early-region tensor Z_early (first launch), the late layers'
+// one- and two-qubit gates and the removal of the crossing bonds between the
+// fixed rows and the open band (Alg. 2).  M, K and N are powers of two and
+// very uneven: one amplitude per batch sums thousands of products into one
+// value, eight open legs are a square 256-column product.  Three kernels
+// share the work (record_late):
+//   k_late_mf   N >= 16: tiles on the FP64 matrix cores
+//   k_late_dot  N < 16, or few rows, with K >= 64: lanes along K
+//   k_late_out  K < 64 otherwise: a thread per output
 __device__ inline double2 to_d2(float2 v) { return make_double2((double)v.x, (double)v.y); }
 __device__ inline double2 to_d2(double2 v) { return v; }
 
@@ -838,13 +844,152 @@ __device__ inline double2 late_in(const LateArgs& a, const TIn* __restrict__ in,
   }
 }
 
-template <typename TIn, int S>
-__device__ __attribute__((always_inline)) inline void late_body(const LateArgs& a, uint32_t bx, uint32_t by) {
-  __shared__ double2 As[16][65];
-  __shared__ double2 Bs[16][65];
+// Lanes along K: a wave takes RB consecutive rows and NC columns, lane l the
+// products kk = l, l + 64, ...; KS waves of the block share a row group and
+// split its K.  J is read once per RB rows, the tensor once per column group
+// with 512-byte runs.  The 64 lanes' partial sums are halved against each
+// other (lane_reduce), the KS waves' sums meet in LDS.  Bound by the read of
+// the tensor.  A 64 x 64-tile kernel took 64 columns of arithmetic for these
+// one to eight: 282 us for one amplitude at w = 10 and 1582 us for the 2^25
+// entries of a bond-four circuit of 26 layers (256 MiB), against 7 us and 121 us
+// (2.2 TB/s) here.  Conditional loads of the rows past M made the compiler wait
+// on each (177 us).
+template <int V>
+__device__ __attribute__((always_inline)) inline double lane_reduce(double (&v)[V], int lane) {
+  int mask = 32;
+#pragma unroll
+  for (int h = V / 2; h >= 1; h >>= 1, mask >>= 1) {
+    const bool up = (lane & mask) != 0;
+#pragma unroll
+    for (int i = 0; i < h; ++i) {
+      const double send = up ? v[i] : v[i + h];
+      v[i] = (up ? v[i + h] : v[i]) + __shfl_xor(send, mask);
+    }
+  }
+  for (; mask >= 1; mask >>= 1) v[0] += __shfl_xor(v[0], mask);
+  return v[0];
+}
+
+template <typename TIn, int S, int NC, int RB>
+__device__ __attribute__((always_inline)) inline void late_dot_body(const LateArgs& a, uint32_t bx, uint32_t by) {
+  constexpr int V = RB * NC * 2;  // real sums of a wave, at most 64
+  static_assert(V <= 64, "one sum per lane");
+  __shared__ double part[4][V];
   const int b = by;
-  const int tilesN = (a.N + 63) / 64;
-  const int tilesM = (a.M + 63) / 64;
+  const int KS = a.K >= 256 ? 4 : a.K >= 128 ? 2 : 1;
+  const int WR = 4 / KS;
+  const int groups = a.N / NC;
+  const int col0 = (int)(bx % (uint32_t)groups) * NC;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const int wk = wave % KS, wr = wave / KS;
+  const int row0 = ((int)(bx / (uint32_t)groups) * WR + wr) * RB;
+  const int var = a.xrow >= 0 ? (int)(a.bits[(size_t)b * a.n + a.xrow] & 1) : 0;
+  const double2* __restrict__ J = a.J + (size_t)var * a.K * a.N + col0;
+  const TIn* __restrict__ in = reinterpret_cast<const TIn*>(a.in) + (size_t)b * a.in_batch_stride;
+  double v[V];
+#pragma unroll
+  for (int i = 0; i < V; ++i) v[i] = 0.0;
+  // K is a power of two; every row group starts at another slice of it, or all
+  // blocks would read the same offsets of their rows at once, which fall on
+  // the same few memory channels
+  const int slices = a.K / (64 * KS);
+  for (int it = 0; it < slices; ++it) {
+    const int kk = (((it + (int)(bx / (uint32_t)groups)) & (slices - 1)) * KS + wk) * 64 + lane;
+    double2 x[RB], z[NC];
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+      x[r] = late_in<TIn, S>(a, in, b, (uint64_t)min(row0 + r, a.M - 1) * a.K + kk);  // (no branch: loads in flight)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) z[c] = J[(size_t)kk * a.N + c];
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        v[2 * (r * NC + c)] += x[r].x * z[c].x - x[r].y * z[c].y;
+        v[2 * (r * NC + c) + 1] += x[r].x * z[c].y + x[r].y * z[c].x;
+      }
+  }
+  const double sum = lane_reduce<V>(v, lane);
+  // after the halvings lane l holds sum l / (64 / V)
+  constexpr int kLanes = 64 / V;
+  if (lane % kLanes == 0) part[wave][lane / kLanes] = sum;
+  __syncthreads();
+  double* out = reinterpret_cast<double*>(a.out + (size_t)b * a.out_batch_stride);
+  for (int i = threadIdx.x; i < V * WR; i += kBlock) {
+    const int g = i / V, q = i % V;
+    double t = 0.0;
+    for (int w = 0; w < KS; ++w) t += part[g * KS + w][q];
+    const int row = ((int)(bx / (uint32_t)groups) * WR + g) * RB + q / (2 * NC);
+    if (row < a.M) out[2 * ((size_t)row * a.N + col0) + q % (2 * NC)] = t;
+  }
+}
+
+template <typename TIn, int S, int NC, int RB>
+__global__ __launch_bounds__(kBlock) void k_late_dot(LateArgs a) {
+  late_dot_body<TIn, S, NC, RB>(a, blockIdx.x, blockIdx.y);
+}
+
+template <typename TIn, int S, int NC, int RB>
+__global__ __launch_bounds__(kBlock) void k_late_dot_g(const Seg<LateArgs>* __restrict__ segs) {
+  const Seg<LateArgs>* s = group_seg(segs);
+  if (!s) return;
+  const LateArgs a = s->a;
+  late_dot_body<TIn, S, NC, RB>(a, blockIdx.x, blockIdx.y);
+}
+
+// One thread per output: with K < 64 a row and J's columns stay in the L1
+// cache, neighbouring threads share a row's entries and read J in runs.
+template <typename TIn, int S>
+__device__ __attribute__((always_inline)) inline void late_out_body(const LateArgs& a, uint32_t bx, uint32_t by) {
+  const int b = by;
+  const long long o = (long long)bx * kBlock + threadIdx.x;
+  if (o >= (long long)a.M * a.N) return;
+  const int col = (int)(o % a.N);
+  const uint64_t row = (uint64_t)(o / a.N);
+  const int var = a.xrow >= 0 ? (int)(a.bits[(size_t)b * a.n + a.xrow] & 1) : 0;
+  const double2* __restrict__ J = a.J + (size_t)var * a.K * a.N + col;
+  const TIn* __restrict__ in = reinterpret_cast<const TIn*>(a.in) + (size_t)b * a.in_batch_stride;
+  double2 acc = make_double2(0.0, 0.0);
+#pragma unroll 8
+  for (int kk = 0; kk < a.K; ++kk) {
+    const double2 x = late_in<TIn, S>(a, in, b, row * a.K + kk);
+    const double2 z = J[(size_t)kk * a.N];
+    acc.x += x.x * z.x - x.y * z.y;
+    acc.y += x.x * z.y + x.y * z.x;
+  }
+  a.out[(size_t)b * a.out_batch_stride + o] = acc;
+}
+
+template <typename TIn, int S>
+__global__ __launch_bounds__(kBlock) void k_late_out(LateArgs a) { late_out_body<TIn, S>(a, blockIdx.x, blockIdx.y); }
+
+template <typename TIn, int S>
+__global__ __launch_bounds__(kBlock) void k_late_out_g(const Seg<LateArgs>* __restrict__ segs) {
+  const Seg<LateArgs>* s = group_seg(segs);
+  if (!s) return;
+  const LateArgs a = s->a;
+  late_out_body<TIn, S>(a, blockIdx.x, blockIdx.y);
+}
+
+// The same contraction on the FP64 matrix cores (v_mfma_f64_16x16x4f64):
+// a 64 x 64 output tile per 256-thread block, 32 x 32 (2 x 2 MFMA tiles)
+// per wave; the complex product takes four real MFMAs per tile and k-step
+// (re += ar*br - ai*bi, im += ar*bi + ai*br).  Lane l supplies A[l%16][k]
+// and B[k][l%16] with k = l/16 and receives D[l/16 + 4q][l%16], q < 4.
+// CT: columns of the block's tile.  Products of 32 or 16 columns take tiles
+// of 128 rows by that many, 32 rows per wave, so no wave multiplies padding.
+typedef double tnc_d4 __attribute__((ext_vector_type(4)));
+
+template <typename TIn, int S, int CT>
+__device__ __attribute__((always_inline)) inline void late_mf_body(const LateArgs& a, uint32_t bx, uint32_t by) {
+  constexpr int RT = CT == 64 ? 64 : 128;  // rows of the block's tile
+  constexpr int WJ = CT >= 32 ? 2 : 1;     // MFMA columns per wave
+  constexpr int QA = RT * 16 / kBlock, QB = CT * 16 / kBlock;
+  __shared__ double2 As[16][RT + 1];
+  __shared__ double2 Bs[16][CT + 1];
+  const int b = by;
+  const int tilesN = (a.N + CT - 1) / CT;
+  const int tilesM = (a.M + RT - 1) / RT;
   // Consecutive block ids go to different XCDs (round robin over 8); the
   // tilesN column blocks of one row tile are given ids that land on the
   // same XCD, so they share its L2 for the row tile.
@@ -853,122 +998,38 @@ __device__ __attribute__((always_inline)) inline void late_body(const LateArgs& 
   const int bn = g % tilesN;
   const int bm = (g / tilesN) * 8 + xcd;
   if (bm >= tilesM) return;
-  const int row0 = bm * 64, col0 = bn * 64;
-  const int var = a.xrow >= 0 ? (int)a.bits[(size_t)b * a.n + a.xrow] : 0;
-  const double2* __restrict__ J = a.J + (size_t)var * a.K * a.N;
-  const TIn* __restrict__ in = reinterpret_cast<const TIn*>(a.in) + (size_t)b * a.in_batch_stride;
-  const int tid = threadIdx.x;
-  const int tr = tid >> 4, tc = tid & 15;
-  double2 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = make_double2(0.0, 0.0);
-  for (int k0 = 0; k0 < a.K; k0 += 16) {
-    for (int e = tid; e < 1024; e += kBlock) {
-      const int r = e >> 4, kk = e & 15;
-      const int row = row0 + r;
-      double2 val = make_double2(0.0, 0.0);
-      if (row < a.M && k0 + kk < a.K) val = late_in<TIn, S>(a, in, b, (uint64_t)row * a.K + k0 + kk);
-      As[kk][r] = val;
-    }
-    for (int e = tid; e < 1024; e += kBlock) {
-      const int kk = e >> 6, c = e & 63;
-      const int col = col0 + c;
-      double2 val = make_double2(0.0, 0.0);
-      if (col < a.N && k0 + kk < a.K) val = J[(size_t)(k0 + kk) * a.N + col];
-      Bs[kk][c] = val;
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int kk = 0; kk < 16; ++kk) {
-      double2 av[4], bv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = As[kk][tr * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bv[j] = Bs[kk][tc * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          acc[i][j].x += av[i].x * bv[j].x - av[i].y * bv[j].y;
-          acc[i][j].y += av[i].x * bv[j].y + av[i].y * bv[j].x;
-        }
-    }
-    __syncthreads();
-  }
-  double2* out = a.out + (size_t)b * a.out_batch_stride;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = row0 + tr * 4 + i;
-    if (row >= a.M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = col0 + tc * 4 + j;
-      if (col < a.N) out[(size_t)row * a.N + col] = acc[i][j];
-    }
-  }
-}
-
-template <typename TIn, int S>
-__global__ __launch_bounds__(kBlock) void k_late(LateArgs a) { late_body<TIn, S>(a, blockIdx.x, blockIdx.y); }
-
-template <typename TIn, int S>
-__global__ __launch_bounds__(kBlock) void k_late_g(const Seg<LateArgs>* __restrict__ segs) {
-  const Seg<LateArgs>* s = group_seg(segs);
-  if (!s) return;
-  const LateArgs a = s->a;
-  late_body<TIn, S>(a, blockIdx.x, blockIdx.y);
-}
-
-// The same contraction on the FP64 matrix cores (v_mfma_f64_16x16x4f64):
-// a 64 x 64 output tile per 256-thread block, 32 x 32 (2 x 2 MFMA tiles)
-// per wave; the complex product takes four real MFMAs per tile and k-step
-// (re += ar*br - ai*bi, im += ar*bi + ai*br).  Lane l supplies A[l%16][k]
-// and B[k][l%16] with k = l/16 and receives D[l/16 + 4q][l%16], q < 4.
-typedef double tnc_d4 __attribute__((ext_vector_type(4)));
-
-template <typename TIn, int S>
-__device__ __attribute__((always_inline)) inline void late_mf_body(const LateArgs& a, uint32_t bx, uint32_t by) {
-  __shared__ double2 As[16][65];
-  __shared__ double2 Bs[16][65];
-  const int b = by;
-  const int tilesN = (a.N + 63) / 64;
-  const int tilesM = (a.M + 63) / 64;
-  const int xcd = bx & 7;
-  const int g = bx >> 3;
-  const int bn = g % tilesN;
-  const int bm = (g / tilesN) * 8 + xcd;
-  if (bm >= tilesM) return;
-  const int row0 = bm * 64, col0 = bn * 64;
+  const int row0 = bm * RT, col0 = bn * CT;
   const int var = a.xrow >= 0 ? (int)a.bits[(size_t)b * a.n + a.xrow] : 0;
   const double2* __restrict__ J = a.J + (size_t)var * a.K * a.N;
   const TIn* __restrict__ in = reinterpret_cast<const TIn*>(a.in) + (size_t)b * a.in_batch_stride;
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63;
-  const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
+  const int wr = CT == 64 ? (wave >> 1) * 32 : wave * 32, wc = CT == 64 ? (wave & 1) * 32 : 0;
   const int li = lane & 15, lk = lane >> 4;
-  tnc_d4 cr[2][2], ci[2][2];
+  tnc_d4 cr[2][WJ], ci[2][WJ];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < WJ; ++j) {
       cr[i][j] = tnc_d4{0.0, 0.0, 0.0, 0.0};
       ci[i][j] = tnc_d4{0.0, 0.0, 0.0, 0.0};
     }
   // the next k-slice of A and B is loaded into registers while the current
-  // one is multiplied from LDS (kBlock = 256 threads: 4 elements each)
-  double2 pa[4], pb[4];
+  // one is multiplied from LDS
+  double2 pa[QA], pb[QB];
   auto fetch = [&](int k0) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < QA; ++q) {
       const int e = tid + q * kBlock;
       const int r = e >> 4, kk = e & 15;
       const int row = row0 + r;
       pa[q] = make_double2(0.0, 0.0);
       if (row < a.M && k0 + kk < a.K) pa[q] = late_in<TIn, S>(a, in, b, (uint64_t)row * a.K + k0 + kk);
-      const int kb = e >> 6, c = e & 63;
-      const int col = col0 + c;
+    }
+#pragma unroll
+    for (int q = 0; q < QB; ++q) {
+      const int e = tid + q * kBlock;
+      const int kb = e / CT, col = col0 + e % CT;
       pb[q] = make_double2(0.0, 0.0);
       if (col < a.N && k0 + kb < a.K) pb[q] = J[(size_t)(k0 + kb) * a.N + col];
     }
@@ -976,25 +1037,29 @@ __device__ __attribute__((always_inline)) inline void late_mf_body(const LateArg
   fetch(0);
   for (int k0 = 0; k0 < a.K; k0 += 16) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < QA; ++q) {
       const int e = tid + q * kBlock;
       As[e & 15][e >> 4] = pa[q];
-      Bs[e >> 6][e & 63] = pb[q];
+    }
+#pragma unroll
+    for (int q = 0; q < QB; ++q) {
+      const int e = tid + q * kBlock;
+      Bs[e / CT][e % CT] = pb[q];
     }
     __syncthreads();
     if (k0 + 16 < a.K) fetch(k0 + 16);
 #pragma unroll
     for (int kc = 0; kc < 4; ++kc) {
       const int kk = kc * 4 + lk;
-      double2 av[2], bv[2];
+      double2 av[2], bv[WJ];
 #pragma unroll
       for (int i = 0; i < 2; ++i) av[i] = As[kk][wr + 16 * i + li];
 #pragma unroll
-      for (int j = 0; j < 2; ++j) bv[j] = Bs[kk][wc + 16 * j + li];
+      for (int j = 0; j < WJ; ++j) bv[j] = Bs[kk][wc + 16 * j + li];
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < WJ; ++j) {
           cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i].x, bv[j].x, cr[i][j], 0, 0, 0);
           cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-av[i].y, bv[j].y, cr[i][j], 0, 0, 0);
           ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i].x, bv[j].y, ci[i][j], 0, 0, 0);
@@ -1007,7 +1072,7 @@ __device__ __attribute__((always_inline)) inline void late_mf_body(const LateArg
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < WJ; ++j)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int row = row0 + wr + 16 * i + lk + 4 * q;
@@ -1016,44 +1081,72 @@ __device__ __attribute__((always_inline)) inline void late_mf_body(const LateArg
       }
 }
 
-template <typename TIn, int S>
-__global__ __launch_bounds__(kBlock) void k_late_mf(LateArgs a) { late_mf_body<TIn, S>(a, blockIdx.x, blockIdx.y); }
+template <typename TIn, int S, int CT>
+__global__ __launch_bounds__(kBlock) void k_late_mf(LateArgs a) { late_mf_body<TIn, S, CT>(a, blockIdx.x, blockIdx.y); }
 
-template <typename TIn, int S>
+template <typename TIn, int S, int CT>
 __global__ __launch_bounds__(kBlock) void k_late_mf_g(const Seg<LateArgs>* __restrict__ segs) {
   const Seg<LateArgs>* s = group_seg(segs);
   if (!s) return;
   const LateArgs a = s->a;
-  late_mf_body<TIn, S>(a, blockIdx.x, blockIdx.y);
+  late_mf_body<TIn, S, CT>(a, blockIdx.x, blockIdx.y);
+}
+
+template <typename TIn, int S, int CT>
+static void pick_late_mf(Launch* L) {
+  L->fn = reinterpret_cast<const void*>(&k_late_mf<TIn, S, CT>);
+  if (S == STORE_C64) L->gfn = reinterpret_cast<const void*>(&k_late_mf_g<TIn, S, CT>);
+}
+
+template <typename TIn, int S, int NC, int RB>
+static void pick_late_dot(Launch* L) {
+  L->fn = reinterpret_cast<const void*>(&k_late_dot<TIn, S, NC, RB>);
+  if (S == STORE_C64) L->gfn = reinterpret_cast<const void*>(&k_late_dot_g<TIn, S, NC, RB>);
+}
+
+// The kernel and grid of a first late launch.  16 columns or more, a K of one
+// MFMA slice and at least 64 rows fill the matrix-core tiles; below that the
+// lanes go along K where K gives every lane of a wave a product, and else a
+// thread computes one output.  RB rows share a read of J: as many as leave
+// one sum per lane, no more than eight.
+template <typename TIn, int S>
+static long long pick_late(const LateArgs& a, Launch* L) {
+  if (a.N >= 16 && a.K >= 16 && a.M >= 64) {
+    const int CT = a.N >= 64 ? 64 : a.N >= 32 ? 32 : 16;
+    const int RT = CT == 64 ? 64 : 128;
+    if (CT == 64) pick_late_mf<TIn, S, 64>(L);
+    else if (CT == 32) pick_late_mf<TIn, S, 32>(L);
+    else pick_late_mf<TIn, S, 16>(L);
+    return (((long long)a.M + RT - 1) / RT + 7) / 8 * 8 * ((a.N + CT - 1) / CT);
+  }
+  if (a.K >= 64) {
+    const int NC = std::min(a.N, 8);
+    const int RB = NC <= 2 ? 8 : NC == 4 ? 4 : 2;
+    if (NC == 1) pick_late_dot<TIn, S, 1, 8>(L);
+    else if (NC == 2) pick_late_dot<TIn, S, 2, 8>(L);
+    else if (NC == 4) pick_late_dot<TIn, S, 4, 4>(L);
+    else pick_late_dot<TIn, S, 8, 2>(L);
+    const int rows = RB * (a.K >= 256 ? 1 : a.K >= 128 ? 2 : 4);
+    return ((long long)a.M + rows - 1) / rows * (a.N / NC);
+  }
+  L->fn = reinterpret_cast<const void*>(&k_late_out<TIn, S>);
+  if (S == STORE_C64) L->gfn = reinterpret_cast<const void*>(&k_late_out_g<TIn, S>);
+  return ((long long)a.M * a.N + kBlock - 1) / kBlock;
 }
 
 hipError_t record_late(const LateArgs& a, bool in_c64, Launch* L) {
   *L = Launch();
   L->cls = 2;
-  const long long tilesM8 = ((long long)(a.M + 63) / 64 + 7) / 8 * 8;
-  const long long tiles = tilesM8 * ((a.N + 63) / 64);
-  // matrix cores for contractions large enough to fill their 16 x 16 tiles
-  const bool mf = in_c64 && a.N >= 32 && a.K >= 16 && a.M >= 64;
-  if (!in_c64) {
-    L->fn = reinterpret_cast<const void*>(&k_late<double2, STORE_C64>);
-    L->gfn = reinterpret_cast<const void*>(&k_late_g<double2, STORE_C64>);
-  } else if (a.store == STORE_F16) {
-    L->fn = mf ? reinterpret_cast<const void*>(&k_late_mf<uint32_t, STORE_F16>)
-               : reinterpret_cast<const void*>(&k_late<uint32_t, STORE_F16>);
-  } else if (a.store == STORE_BF16) {
-    L->fn = mf ? reinterpret_cast<const void*>(&k_late_mf<uint32_t, STORE_BF16>)
-               : reinterpret_cast<const void*>(&k_late<uint32_t, STORE_BF16>);
-  } else if (a.store == STORE_C64) {
-    L->fn = mf ? reinterpret_cast<const void*>(&k_late_mf<float2, STORE_C64>)
-               : reinterpret_cast<const void*>(&k_late<float2, STORE_C64>);
-    L->gfn = mf ? reinterpret_cast<const void*>(&k_late_mf_g<float2, STORE_C64>)
-                : reinterpret_cast<const void*>(&k_late_g<float2, STORE_C64>);
-  } else {
+  if (a.n_batches < 1 || a.M < 1 || a.K < 1 || a.N < 1 || (a.N & (a.N - 1)) != 0 || (a.K & (a.K - 1)) != 0)
     return hipErrorInvalidValue;
-  }
+  long long blocks;
+  if (!in_c64) blocks = pick_late<double2, STORE_C64>(a, L);
+  else if (a.store == STORE_F16) blocks = pick_late<uint32_t, STORE_F16>(a, L);
+  else if (a.store == STORE_BF16) blocks = pick_late<uint32_t, STORE_BF16>(a, L);
+  else if (a.store == STORE_C64) blocks = pick_late<float2, STORE_C64>(a, L);
+  else return hipErrorInvalidValue;
   set_arg(L, a);
-  if (a.n_batches < 1) return hipErrorInvalidValue;
-  return set_shape(L, tiles, (unsigned)a.n_batches, kBlock, 0);
+  return set_shape(L, blocks, (unsigned)a.n_batches, kBlock, 0);
 }
 
 // ---------------------------------------------------------------------------

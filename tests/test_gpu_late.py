@@ -1,0 +1,61 @@
+"""The first late launch (the join with the early region, and the late
+removals folded into it) at the edges of its kernels' ranges, against the
+oracle: products of M rows, K terms and N = 2^k columns per batch, with K below,
+at and above the 64, 128 and 256 terms where lanes and waves start to share a
+row, fewer and more rows than a wave takes, and each column tile of the matrix
+cores.  Tolerances: those of the complex64 and FP16 paths, the late phase
+being FP64."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+CASES = [
+    # n, d, k, late_fold, batches
+    (9, 2, 0, 0, 3),      # K = 2
+    (9, 10, 0, 0, 5),     # one row of K = 32
+    (9, 12, 0, 0, 5),     # one row of K = 64
+    (9, 14, 0, 0, 2),     # 128
+    (9, 16, 0, 0, 2),     # 256
+    (9, 24, 0, 0, 2),     # 4096
+    (9, 26, 0, 0, 2),     # two rows of 4096, N = 2
+    (9, 31, 0, 0, 2),     # odd depth, 8 or 16 rows
+    (9, 16, 1, 4, 2),     # k = 1: K = 32
+    (9, 16, 1, 5, 2),     # 64, M = 4 below the 32 rows of a block
+    (9, 26, 1, 6, 2),     # 128, M = 64
+    (9, 26, 2, 3, 2),     # N = 4, K = 32
+    (9, 26, 2, 4, 2),     # 64
+    (9, 26, 2, 6, 2),     # 256
+    (9, 26, 3, -1, 2),    # N = 8, K = 8
+    (9, 26, 3, 3, 2),     # 64
+    (9, 26, 3, 7, 2),     # 1024, 8 rows
+    (9, 18, 4, -1, 2),    # N = 16: 32 rows, a thread per output
+    (9, 18, 4, 2, 2),     # K = 64, 8 rows: two column groups of eight
+    (9, 20, 4, -1, 2),    # 64 rows: the 16-column tile, half its 128 rows
+    (9, 24, 4, 1, 2),     # 128 rows
+    (9, 22, 5, -1, 2),    # the 32-column tile
+    (9, 26, 5, 2, 2),
+    (9, 24, 6, -1, 2),    # the 64-column tile
+    (9, 20, 5, 1, 2),     # N = 32, 16 rows: K = 64
+]
+
+
+@pytest.mark.parametrize("storage", ["c64", "f16"])
+@pytest.mark.parametrize("n,d,k,fold,nb", CASES)
+def test_first_late_launch(n, d, k, fold, nb, storage):
+    from paper_2608_13110_amd import STORE_C64, STORE_F16_BLOCKSCALE, Plan
+    c = H.mixed_circuit(n, d, 31 * d + k, dense=0.3)
+    bits = W.random_bitstrings(n, nb, W.rng_for(409, d, k))
+    print(f"  [gpu] n={n} d={d} k={k} fold={fold} storage={storage}", flush=True)
+    plan = Plan.from_circuit(c, dict(late_fold=fold) if fold else None)
+    mode = STORE_C64 if storage == "c64" else STORE_F16_BLOCKSCALE
+    got = plan.amplitudes(torch.from_numpy(bits).cuda(), k, storage=mode)
+    torch.cuda.synchronize()
+    per, l2 = H.amp_errors(got.cpu().numpy(), oracle.amplitudes(c, bits, k), n)
+    assert per < (H.TOL_C64 if storage == "c64" else 4e-2), (per, l2)
