@@ -1485,15 +1485,28 @@ hipError_t launch_frugal_accept(const double2* amps, long long count, int n, dou
 
 // log-XEB (Sec. 5.2): F = gamma + n ln 2 + mean_i ln p_i with p_i = |amp|^2
 // of the selected component of each batch (sel == nullptr: every component).
-// One block, FP64 throughout.  result = {F, SE, F - 1.96 SE, F + 1.96 SE, N}.
-__global__ __launch_bounds__(kBlock) void k_logxeb(const double2* amps, int n_batches, int k,
-                                                   const int32_t* sel, int n_qubits, double* result) {
+// FP64 throughout.  result = {F, SE, F - 1.96 SE, F + 1.96 SE, N}.
+__device__ inline void xeb_result(double sum, double sum2, long long total, int n_qubits, double* result) {
+  const double N = (double)total;
+  const double mean = sum / N;
+  const double var = N > 1 ? (sum2 - N * mean * mean) / (N - 1.0) : 0.0;
+  const double se = N > 1 ? sqrt(var > 0 ? var : 0.0) / sqrt(N) : 0.0;
+  const double gamma = 0.57721566490153286060651209008240243;
+  const double F = gamma + (double)n_qubits * 0.69314718055994530941723212145817657 + mean;
+  result[0] = F;
+  result[1] = se;
+  result[2] = F - 1.96 * se;
+  result[3] = F + 1.96 * se;
+  result[4] = N;
+}
+
+// Sums of ln p and (ln p)^2 over this block's share of the components, valid
+// in thread 0.
+__device__ inline double2 xeb_block_sums(const double2* amps, int k, const int32_t* sel, long long total) {
   __shared__ double s1[kBlock], s2[kBlock];
-  const long long per = 1ll << k;
-  const long long total = sel ? (long long)n_batches : (long long)n_batches * per;
   double a1 = 0.0, a2 = 0.0;
-  for (long long i = threadIdx.x; i < total; i += blockDim.x) {
-    const long long idx = sel ? (i * per + sel[i]) : i;
+  for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < total; i += (long long)gridDim.x * kBlock) {
+    const long long idx = sel ? ((i << k) + sel[i]) : i;
     const double2 z = amps[idx];
     const double lp = log(z.x * z.x + z.y * z.y);
     a1 += lp;
@@ -1502,32 +1515,93 @@ __global__ __launch_bounds__(kBlock) void k_logxeb(const double2* amps, int n_ba
   s1[threadIdx.x] = a1;
   s2[threadIdx.x] = a2;
   __syncthreads();
-  for (int off = blockDim.x / 2; off > 0; off >>= 1) {
+  for (int off = kBlock / 2; off > 0; off >>= 1) {
     if ((int)threadIdx.x < off) {
       s1[threadIdx.x] += s1[threadIdx.x + off];
       s2[threadIdx.x] += s2[threadIdx.x + off];
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    const double N = (double)total;
-    const double mean = s1[0] / N;
-    const double var = N > 1 ? (s2[0] - N * mean * mean) / (N - 1.0) : 0.0;
-    const double se = N > 1 ? sqrt(var > 0 ? var : 0.0) / sqrt(N) : 0.0;
-    const double gamma = 0.57721566490153286060651209008240243;
-    const double F = gamma + (double)n_qubits * 0.69314718055994530941723212145817657 + mean;
-    result[0] = F;
-    result[1] = se;
-    result[2] = F - 1.96 * se;
-    result[3] = F + 1.96 * se;
-    result[4] = N;
+  return make_double2(s1[0], s2[0]);
+}
+
+__global__ __launch_bounds__(kBlock) void k_logxeb(const double2* amps, long long total, int k, const int32_t* sel,
+                                                   int n_qubits, double* result) {
+  const double2 s = xeb_block_sums(amps, k, sel, total);
+  if (threadIdx.x == 0) xeb_result(s.x, s.y, total, n_qubits, result);
+}
+
+// Many blocks: each adds its two sums to the caller's result buffer, and the
+// last to arrive turns them into the result.  The sums go in as integers, two
+// words each (k_logxeb_clear zeroes all five): a fixed-point value v is
+// hi * q + lo * q / 2^40, q a power of two that keeps the total below 2^62.
+// Integer sums do not depend on the order of arrival, so the result is the
+// same from run to run, and their 100 bits add no rounding of note.  One block
+// computes 2051 x 256 logarithms in 780 us (one CU), 128 blocks in 17 us.
+constexpr int kXebBlocks = 128;  // (their sums meet at five addresses: 512 blocks took 37 us)
+constexpr long long kXebSingle = 4096;  // up to here one block is as fast (8 us) and needs no clearing launch
+static_assert(kXebBlocks < (1 << 12), "arrival fields of 16 bits, low words of 40 bits");
+
+// ln p of a finite nonzero double lies in (-746, 710): |sum| < total 2^10 and
+// sum of squares < total 2^20; the quantum of the sum (p = 1) or of the squares (p = 2)
+__device__ inline int xeb_shift(long long total, int p) { return 64 - __clzll(total) + 10 * p - 62; }
+
+__device__ inline void xeb_add(unsigned long long* acc, double v, int shift) {
+  const double u = ldexp(v, -shift);
+  const double hi = rint(u);
+  atomicAdd(acc, (unsigned long long)(long long)hi);
+  atomicAdd(acc + 1, (unsigned long long)(long long)rint(ldexp(u - hi, 40)));
+}
+
+__device__ inline double xeb_value(unsigned long long* acc, int shift) {
+  const long long hi = (long long)atomicAdd(acc, 0ull), lo = (long long)atomicAdd(acc + 1, 0ull);
+  return ldexp((double)hi + ldexp((double)lo, -40), shift);
+}
+
+__global__ void k_logxeb_clear(unsigned long long* acc) {
+  if (threadIdx.x < 5) acc[threadIdx.x] = 0ull;
+}
+
+__global__ __launch_bounds__(kBlock) void k_logxeb_blocks(const double2* amps, long long total, int k,
+                                                          const int32_t* sel, int n_qubits, double* result) {
+  const double2 s = xeb_block_sums(amps, k, sel, total);
+  if (threadIdx.x != 0) return;
+  // word 4: arrivals, and how many sums were -inf (a zero probability), +inf, NaN
+  unsigned long long* acc = reinterpret_cast<unsigned long long*>(result);
+  unsigned long long mark = 1ull;
+  if (isfinite(s.x) && isfinite(s.y)) {
+    xeb_add(acc, s.x, xeb_shift(total, 1));
+    xeb_add(acc + 2, s.y, xeb_shift(total, 2));
+  } else {
+    mark |= isnan(s.x) ? 1ull << 48 : s.x > 0.0 ? 1ull << 32 : 1ull << 16;
   }
+  __threadfence();
+  const unsigned long long seen = atomicAdd(acc + 4, mark) + mark;
+  if ((seen & 0xffffull) != gridDim.x) return;
+  __threadfence();
+  double sum = xeb_value(acc, xeb_shift(total, 1)), sum2 = xeb_value(acc + 2, xeb_shift(total, 2));
+  if (seen >> 16) {
+    if ((seen >> 16) & 0xffffull) sum -= INFINITY;
+    if ((seen >> 32) & 0xffffull) sum += INFINITY;
+    if (seen >> 48) sum = NAN;
+    sum2 = isnan(sum) && (seen >> 48) ? NAN : INFINITY;
+  }
+  xeb_result(sum, sum2, total, n_qubits, result);
 }
 
 hipError_t launch_logxeb(const double2* amps, int n_batches, int k, const int32_t* sel, int n_qubits,
                          double* result, hipStream_t s) {
-  return launch_direct(reinterpret_cast<const void*>(&k_logxeb), dim3(1), dim3(kBlock), s, amps, n_batches, k, sel,
-                       n_qubits, result);
+  const long long total = sel ? (long long)n_batches : (long long)n_batches << k;
+  if (total <= kXebSingle)
+    return launch_direct(reinterpret_cast<const void*>(&k_logxeb), dim3(1), dim3(kBlock), s, amps, total, k, sel,
+                         n_qubits, result);
+  const hipError_t e = launch_direct(reinterpret_cast<const void*>(&k_logxeb_clear), dim3(1), dim3(64), s,
+                                     reinterpret_cast<unsigned long long*>(result));
+  if (e != hipSuccess) return e;
+  // at least four components per thread
+  const long long blocks = std::min<long long>(kXebBlocks, (total + 4 * kBlock - 1) / (4 * kBlock));
+  return launch_direct(reinterpret_cast<const void*>(&k_logxeb_blocks), dim3((unsigned)blocks), dim3(kBlock), s, amps,
+                       total, k, sel, n_qubits, result);
 }
 
 }  // namespace tnc
