@@ -1151,10 +1151,17 @@ hipError_t record_late(const LateArgs& a, bool in_c64, Launch* L) {
 
 // ---------------------------------------------------------------------------
 // Late program on the shrinking tensor, FP64.  A block loads 2^j consecutive
-// rows of 2^s state entries into LDS; one- and two-qubit gates act on the
-// state bits of every live row, a removal sums the lowest remaining row bit
-// against C_u on state bit 0 (Alg. 2, the late ContractLayer steps).  After
-// l removals the live rows are those whose low l row bits are zero.
+// rows of 2^s state entries into LDS; two-qubit gates act on the state bits of
+// every live row, a removal sums the lowest remaining row bit against C_u on
+// state bit 0 (Alg. 2, the late ContractLayer steps).  After l removals the
+// live rows are those whose low l row bits are zero.  The ops are a serial
+// chain of LDS round trips, so their latency counts: the program is staged in
+// LDS first (read from memory op by op, its header and then its matrix cost
+// two cache misses per op), and a thread per group of four entries, up to 512,
+// keeps each op to one or two rounds.  w = 17, k = 5, one batch: 120 us for
+// both launches before (with the one-qubit gates as ops of their own), 47 us
+// now; 64 batches of w = 20, k = 6: 2.60 ms before, 1.23 ms now.
+constexpr int kLateStage = 48;  // ops staged at a time (13 KiB)
 __device__ inline double2 zfma2(double2 m0, double2 x0, double2 m1, double2 x1) {
   return make_double2(m0.x * x0.x - m0.y * x0.y + m1.x * x1.x - m1.y * x1.y,
                       m0.x * x0.y + m0.y * x0.x + m1.x * x1.y + m1.y * x1.x);
@@ -1173,12 +1180,21 @@ __device__ __attribute__((always_inline)) inline void late_ops_body(const LateOp
   const int total = 1 << (sb + a.j);
   const double2* in = a.in + (size_t)b * a.in_batch_stride + ((size_t)row_out << (a.j + sb));
   for (int i = threadIdx.x; i < total; i += blockDim.x) st[i] = in[i];
-  __syncthreads();
+  LateOpDev* prog = reinterpret_cast<LateOpDev*>(st + total);
   int l = 0;
   for (int o = 0; o < a.n_prog; ++o) {
-    const LateOpDev& op = a.prog[o];
+    const int at = o % kLateStage;
+    if (at == 0) {  // the next ops of the program (every thread is past the last ones: barrier below)
+      constexpr int kWords = sizeof(LateOpDev) / 16;
+      const int words = min(kLateStage, a.n_prog - o) * kWords;
+      const uint4* src = reinterpret_cast<const uint4*>(a.prog + o);
+      for (int i = threadIdx.x; i < words; i += blockDim.x) reinterpret_cast<uint4*>(prog)[i] = src[i];
+      __syncthreads();
+    }
+    const LateOpDev& op = prog[at];
+    const int kind = __builtin_amdgcn_readfirstlane(op.kind);
     const int live = a.j - l;
-    if (op.kind == 1) {
+    if (kind == 1) {
       const int items = (1 << live) << (sb - 1);
       for (int w = threadIdx.x; w < items; w += blockDim.x) {
         const int r = (w >> (sb - 1)) << l;
@@ -1188,7 +1204,7 @@ __device__ __attribute__((always_inline)) inline void late_ops_body(const LateOp
         st[i0] = zfma2(op.m[0], x0, op.m[1], x1);
         st[i1] = zfma2(op.m[2], x0, op.m[3], x1);
       }
-    } else if (op.kind == 2) {
+    } else if (kind == 2) {
       const int items = (1 << live) << (sb - 2);
       for (int w = threadIdx.x; w < items; w += blockDim.x) {
         const int r = (w >> (sb - 2)) << l;
@@ -1207,7 +1223,7 @@ __device__ __attribute__((always_inline)) inline void late_ops_body(const LateOp
 #pragma unroll
         for (int u = 0; u < 4; ++u) st[idx[u]] = y[u];
       }
-    } else if (op.kind == 3) {
+    } else if (kind == 3) {
       // an output-bit variant (xrow >= 0) takes the second set of matrices
       const double2* m = op.m + ((op.xrow >= 0 && (a.bits[(size_t)b * a.n + op.xrow] & 1)) ? 8 : 0);
       const int items = (1 << (live - 1)) << (sb - 1);
@@ -1223,7 +1239,7 @@ __device__ __attribute__((always_inline)) inline void late_ops_body(const LateOp
         st[ia | 1] = make_double2(o1a.x + o1b.x, o1a.y + o1b.y);
       }
       ++l;
-    } else if (op.kind == 6) {
+    } else if (kind == 6) {
       // two slots (l, l+1) at once: row u = bit l + 2 bit (l+1) takes C_u
       const int items = (1 << (live - 2)) << (sb - 1);
       for (int w = threadIdx.x; w < items; w += blockDim.x) {
@@ -1247,6 +1263,7 @@ __device__ __attribute__((always_inline)) inline void late_ops_body(const LateOp
     }
     __syncthreads();
   }
+  if (a.n_prog == 0) __syncthreads();
   double2* out = a.out + (size_t)b * a.out_batch_stride;
   if (a.final_kind == 5) {
     for (int bb = threadIdx.x; bb < (1 << a.k); bb += blockDim.x) {
@@ -1264,12 +1281,12 @@ __device__ __attribute__((always_inline)) inline void late_ops_body(const LateOp
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_late_ops(LateOpsArgs a) {
+__global__ __launch_bounds__(512) void k_late_ops(LateOpsArgs a) {
   extern __shared__ double2 st[];
   late_ops_body(a, st, blockIdx.x, blockIdx.y);
 }
 
-__global__ __launch_bounds__(kBlock) void k_late_ops_g(const Seg<LateOpsArgs>* __restrict__ segs) {
+__global__ __launch_bounds__(512) void k_late_ops_g(const Seg<LateOpsArgs>* __restrict__ segs) {
   extern __shared__ double2 st[];
   const Seg<LateOpsArgs>* s = group_seg(segs);
   if (!s) return;
@@ -1280,11 +1297,14 @@ __global__ __launch_bounds__(kBlock) void k_late_ops_g(const Seg<LateOpsArgs>* _
 hipError_t record_late_ops(const LateOpsArgs& a, Launch* L) {
   *L = Launch();
   L->cls = 2;
-  if (a.s + a.j > 12 || a.n_batches < 1) return hipErrorInvalidValue;
+  if (a.s + a.j > 12 || a.n_batches < 1 || a.n_prog < 0) return hipErrorInvalidValue;
+  static_assert(sizeof(LateOpDev) % 16 == 0 && alignof(LateOpDev) <= 16, "staged as 16-byte words");
+  const int threads = std::max(64, std::min(512, 1 << std::max(0, a.s + a.j - 2)));
+  const size_t lds = (sizeof(double2) << (a.s + a.j)) + sizeof(LateOpDev) * (size_t)std::min(kLateStage, a.n_prog);
   L->fn = reinterpret_cast<const void*>(&k_late_ops);
   L->gfn = reinterpret_cast<const void*>(&k_late_ops_g);
   set_arg(L, a);
-  return set_shape(L, a.rows_out, (unsigned)a.n_batches, kBlock, sizeof(double2) << (a.s + a.j));
+  return set_shape(L, a.rows_out, (unsigned)a.n_batches, (unsigned)threads, lds);
 }
 
 // ---------------------------------------------------------------------------

@@ -7,37 +7,46 @@ namespace tnc {
 
 namespace {
 
-// cols[c * dim + t]: column c of a dim x dim operator, as a state vector.
-void cols_u1(std::vector<cd>& cols, int sb, int bit, const cd* m) {
-  const int dim = 1 << sb;
-  for (int c = 0; c < dim; ++c) {
-    cd* v = cols.data() + (size_t)c * dim;
-    for (int i = 0; i < dim; ++i) {
-      if (i >> bit & 1) continue;
-      const int i1 = i | (1 << bit);
-      const cd a0 = v[i], a1 = v[i1];
-      v[i] = m[0] * a0 + m[1] * a1;
-      v[i1] = m[2] * a0 + m[3] * a1;
+// A 2x2 on bit `bit`, or a 4x4 on bits (bit, bit + 1), of `rows` states of
+// 2^sb entries each (FP64, real and imaginary parts spelled out: the library's
+// complex product checks for NaN).
+void apply_u1(cd* st, size_t rows, int sb, int bit, const cd* m) {
+  const size_t total = rows << sb, h = size_t(1) << bit;
+  double k[8];
+  for (int e = 0; e < 4; ++e) k[2 * e] = m[e].real(), k[2 * e + 1] = m[e].imag();
+  double* v = reinterpret_cast<double*>(st);
+  for (size_t i0 = 0; i0 < total; i0 += 2 * h)
+    for (size_t i = i0; i < i0 + h; ++i) {
+      double* a = v + 2 * i;
+      double* b = v + 2 * (i + h);
+      const double ax = a[0], ay = a[1], bx = b[0], by = b[1];
+      a[0] = k[0] * ax - k[1] * ay + k[2] * bx - k[3] * by;
+      a[1] = k[0] * ay + k[1] * ax + k[2] * by + k[3] * bx;
+      b[0] = k[4] * ax - k[5] * ay + k[6] * bx - k[7] * by;
+      b[1] = k[4] * ay + k[5] * ax + k[6] * by + k[7] * bx;
     }
-  }
 }
 
-void cols_g4(std::vector<cd>& cols, int sb, int bit, const cd* g) {
-  const int dim = 1 << sb;
-  for (int c = 0; c < dim; ++c) {
-    cd* v = cols.data() + (size_t)c * dim;
-    for (int i = 0; i < dim; ++i) {
-      if ((i >> bit & 1) || (i >> (bit + 1) & 1)) continue;
-      const int idx[4] = {i, i | (1 << (bit + 1)), i | (1 << bit), i | (1 << bit) | (1 << (bit + 1))};
-      cd a[4], r[4];
-      for (int u = 0; u < 4; ++u) a[u] = v[idx[u]];
+void apply_g4(cd* st, size_t rows, int sb, int bit, const cd* g) {
+  const size_t total = rows << sb, h = size_t(1) << bit;
+  double* v = reinterpret_cast<double*>(st);
+  for (size_t i0 = 0; i0 < total; i0 += 4 * h)
+    for (size_t i = i0; i < i0 + h; ++i) {
+      // basis 2 bit_a + bit_{a+1}
+      double* p[4] = {v + 2 * i, v + 2 * (i + 2 * h), v + 2 * (i + h), v + 2 * (i + 3 * h)};
+      double x[4], y[4];
+      for (int u = 0; u < 4; ++u) x[u] = p[u][0], y[u] = p[u][1];
       for (int o = 0; o < 4; ++o) {
-        r[o] = 0;
-        for (int u = 0; u < 4; ++u) r[o] += g[4 * o + u] * a[u];
+        double re = 0, im = 0;
+        for (int u = 0; u < 4; ++u) {
+          const double kr = g[4 * o + u].real(), ki = g[4 * o + u].imag();
+          re += kr * x[u] - ki * y[u];
+          im += kr * y[u] + ki * x[u];
+        }
+        p[o][0] = re;
+        p[o][1] = im;
       }
-      for (int u = 0; u < 4; ++u) v[idx[u]] = r[u];
     }
-  }
 }
 
 int bitrev(int b, int k) {
@@ -74,7 +83,7 @@ int build_late(const Plan& p, const Schedule& s, LatePlan* out, std::string* err
   const int nrem = int(rpos.size());
   // k = 0: fold removals of up to 12 slots (the state is one qubit), but not
   // a removal with an output-bit variant (the first launch has one variant
-  // row, the final one's).  k >= 1: folding j removals costs O(2^(3k+j)) on
+  // row, the final one's).  k >= 1: folding j removals costs O(k 2^(2k+j)) on
   // the host and shrinks the first launch's FP64 output to 2^(m-j) rows;
   // worth it for large tensors only.  With no removal folded, the join
   // matrix is Z_early itself and every late op runs on the device.
@@ -84,9 +93,8 @@ int build_late(const Plan& p, const Schedule& s, LatePlan* out, std::string* err
     while (j1 < nrem && slots_to[j1 + 1] <= 12 && L[rpos[j1]].xrow < 0) ++j1;
   } else {
     // 2^35-entry tensors (256 GiB of complex64) leave room for a join output
-    // of 2^(h-j) x 16 B only with j = 7 (4 GiB; the fold takes ~4 s).  From
-    // 2^30 entries on, j = 5 shrinks the late launches' input 32-fold for a
-    // host fold of about a second; the join's flops do not depend on j.
+    // of 2^(h-j) x 16 B only with j = 7 (4 GiB).  From 2^30 entries on, j = 5
+    // shrinks the late launches' input 32-fold; the join's flops do not depend on j.
     const int want = p.opt.late_fold == 0 ? (s.m_fix >= 35 ? 7 : s.m_fix >= 30 ? 5 : s.m_fix >= 26 ? 3 : 0)
                                           : std::max(0, p.opt.late_fold);
     j1 = std::min(nrem, std::min(want, k <= 8 ? 8 : 1));
@@ -94,65 +102,33 @@ int build_late(const Plan& p, const Schedule& s, LatePlan* out, std::string* err
   const bool first_final = j1 == nrem;
   const int first_end = first_final ? nbody : (j1 == 0 ? 0 : rpos[j1 - 1] + 1);
 
-  // P_u for each assignment u of the folded slots
+  // The rows of J: the states that enter the late program (Z_early's rows, or
+  // the start vector) taken through the folded ops, doubled at each removal
+  // (row u * 2^ub + ue: bit l of u the value of the l-th folded slot).
   const int js = slots_to[j1];
-  const int nu = 1 << js;
-  std::vector<std::vector<cd>> P(nu);
-  for (int u = 0; u < nu; ++u) {
-    std::vector<cd> cols((size_t)dim * dim, cd(0));
-    for (int c = 0; c < dim; ++c) cols[(size_t)c * dim + c] = 1;
-    int l = 0;
-    for (int i = 0; i < first_end; ++i) {
-      const LateOp& o = L[i];
-      if (o.kind == L_U1) cols_u1(cols, sb, o.a, o.m.data());
-      else if (o.kind == L_G4) cols_g4(cols, sb, o.a, o.m.data());
-      else if (o.kind == L_REMOVE) {
-        const int b = (u >> l) & 1;
-        cols_u1(cols, sb, 0, o.m.data() + 4 * b);
-        ++l;
-      } else if (o.kind == L_REMOVE2) {
-        const int b = (u >> l) & 3;
-        cols_u1(cols, sb, 0, o.m.data() + 4 * b);
-        l += 2;
+  const int ub = s.join_u_bits;
+  const size_t de = size_t(1) << ub;
+  std::vector<cd> Ju(s.join.begin(), s.join.begin() + de * dim);
+  for (int i = 0; i < first_end; ++i) {
+    const LateOp& o = L[i];
+    const size_t rows = Ju.size() >> sb;
+    if (o.kind == L_U1) apply_u1(Ju.data(), rows, sb, o.a, o.m.data());
+    else if (o.kind == L_G4) apply_g4(Ju.data(), rows, sb, o.a, o.m.data());
+    else {
+      const int nu = o.kind == L_REMOVE2 ? 4 : 2;
+      const size_t part = Ju.size();
+      Ju.resize(part * nu);
+      for (int u = nu - 1; u >= 0; --u) {
+        if (u > 0) std::copy(Ju.begin(), Ju.begin() + part, Ju.begin() + part * u);
+        apply_u1(Ju.data() + part * u, rows, sb, 0, o.m.data() + 4 * u);
       }
     }
-    P[u].swap(cols);
   }
   LateFirst& F = out->first;
   F.j = js;
   F.final = first_final;
-  const int ub = s.join_u_bits;
   F.K = 1 << (ub + js);
   F.M = 1LL << (s.m_fix - ub - js);
-  // unpermuted J: Ju[kk][t]
-  std::vector<cd> Ju((size_t)F.K * dim, cd(0));
-  for (int u = 0; u < nu; ++u) {
-    const std::vector<cd>& cols = P[u];
-    if (k == 0) {
-      // kk = u; state entering = v (the join vector)
-      for (int t = 0; t < dim; ++t) {
-        cd acc = 0;
-        for (int w = 0; w < dim; ++w) acc += cols[(size_t)w * dim + t] * s.join[w];
-        Ju[(size_t)u * dim + t] = acc;
-      }
-    } else {
-      const int de = 1 << ub;
-      if (first_end == 0) {
-        // nothing folded: P is the identity and J is the join matrix
-        std::copy(s.join.begin(), s.join.begin() + (size_t)de * dim, Ju.begin() + ((size_t)u << ub) * dim);
-        continue;
-      }
-      for (int ue = 0; ue < de; ++ue) {
-        cd* row = Ju.data() + ((size_t)((u << ub) | ue)) * dim;
-        for (int tp = 0; tp < dim; ++tp) {
-          const cd z = s.join[(size_t)ue * dim + tp];
-          if (z == cd(0)) continue;
-          const cd* col = cols.data() + (size_t)tp * dim;
-          for (int t = 0; t < dim; ++t) row[t] += z * col[t];
-        }
-      }
-    }
-  }
   if (!first_final) {
     F.N = dim;
     F.nvar = 1;

@@ -1092,6 +1092,91 @@ bool merge_into_dense(SweepOp& a, SweepOp& b, const SweepOp& e) {
   return true;
 }
 
+// Absorbs the one-qubit gates of a late program into the gates and removals
+// they meet (the next op on their state bit, else the last one, else the final
+// contraction): in brickwork every one of them, so an LDS round trip per
+// two-qubit gate and removal is left, a third of the ops.
+void absorb_one_qubit_gates(std::vector<LateOp>* prog, int s_bits) {
+  if (prog->empty()) return;
+  std::vector<M2> pend(s_bits);      // gates since the bit's last op
+  std::vector<char> has(s_bits, 0);
+  std::vector<int> last(s_bits, -1);  // index in `out` of the last op on the bit
+  std::vector<LateOp> out;
+  // every 2x2 C in m[0..count): C X (right) or X C (left)
+  auto mul_all = [](std::vector<cd>& m, const M2& X, bool right) {
+    for (size_t q = 0; q + 4 <= m.size(); q += 4) {
+      M2 C;
+      for (int e = 0; e < 4; ++e) C.a[e] = m[q + e];
+      C = right ? C * X : X * C;
+      for (int e = 0; e < 4; ++e) m[q + e] = C.a[e];
+    }
+  };
+  // the 4x4 g times (U on the upper bit, V on the lower), right or left
+  auto mul_g4 = [](std::vector<cd>& g, const M2& U, const M2& V, bool right) {
+    std::vector<cd> r(16, cd(0));
+    for (int o = 0; o < 4; ++o)
+      for (int i = 0; i < 4; ++i)
+        for (int t = 0; t < 4; ++t) {
+          if (right) r[4 * o + i] += g[4 * o + t] * (U(t >> 1, i >> 1) * V(t & 1, i & 1));
+          else r[4 * o + i] += (U(o >> 1, t >> 1) * V(o & 1, t & 1)) * g[4 * t + i];
+        }
+    g.swap(r);
+  };
+  for (const LateOp& op : *prog) {
+    const int at = int(out.size());
+    if (op.kind == L_U1) {
+      M2 u;
+      for (int e = 0; e < 4; ++e) u.a[e] = op.m[e];
+      pend[op.a] = has[op.a] ? u * pend[op.a] : u;
+      has[op.a] = 1;
+      continue;
+    }
+    LateOp o = op;
+    if (op.kind == L_G4) {
+      if (has[op.a] || has[op.a + 1]) mul_g4(o.m, pend[op.a], pend[op.a + 1], true);
+      for (int b : {op.a, op.a + 1}) {
+        pend[b] = M2();
+        has[b] = 0;
+        last[b] = at;
+      }
+    } else if (op.kind == L_REMOVE || op.kind == L_REMOVE2) {
+      if (has[0]) mul_all(o.m, pend[0], true);
+      pend[0] = M2();
+      has[0] = 0;
+      last[0] = at;
+    } else {  // the final contraction
+      if (op.kind == L_DOT && has[0]) {
+        for (int x = 0; x < 2; ++x) {
+          cd f[2];
+          rowvec_mul(&op.m[2 * x], pend[0], f);
+          o.m[2 * x] = f[0];
+          o.m[2 * x + 1] = f[1];
+        }
+        has[0] = 0;
+      }
+      for (int b = 0; b < s_bits; ++b) {
+        if (!has[b]) continue;
+        if (last[b] < 0) {
+          LateOp u;
+          u.kind = L_U1;
+          u.a = b;
+          for (int e = 0; e < 4; ++e) u.m.push_back(pend[b].a[e]);
+          out.push_back(u);
+        } else if (out[last[b]].kind == L_G4) {
+          LateOp& g = out[last[b]];
+          if (g.a == b) mul_g4(g.m, pend[b], M2(), false);
+          else mul_g4(g.m, M2(), pend[b], false);
+        } else {
+          mul_all(out[last[b]].m, pend[b], false);
+        }
+        has[b] = 0;
+      }
+    }
+    out.push_back(o);
+  }
+  prog->swap(out);
+}
+
 // The schedule of a bond-dimension-four plan (k = 0): rows 1..n-2 as dense
 // 4x4 updates, the end 2x2 of each row merged into the 4x4 before it, and
 // the last row as the late program.
@@ -1150,6 +1235,7 @@ int schedule4(Plan& p, Schedule& s, std::string* err) {
   s.passes = plan_passes(p, s.ops, s.reg_bits);
   int rc = build_late4(p, s, err);
   if (rc) return rc;
+  absorb_one_qubit_gates(&s.late, s.s_bits);
   // Cost in the |I||J||K| convention of Sec. 2.2: a crossing above absorbed
   // with its worldline piece costs 2^(W+3) (two steps of 2^(W+2)), the end
   // piece of a row 2^(W+1); build-up and the last row as for bond two.
@@ -1322,6 +1408,7 @@ int get_schedule(Plan& p, int k, std::shared_ptr<Schedule>* out, std::string* er
     s->late.push_back(o);
     if (s->n_remove != s->m_fix - k) return fail(err, kErrInvalid, "late removals do not match the live slots");
   }
+  absorb_one_qubit_gates(&s->late, s->s_bits);
   // Cost model in the |I||J||K| convention of Sec. 2.2: a paired update of
   // an R-leg boundary tensor costs 2^(R+2), a single absorption 2^(R+1).
   {
