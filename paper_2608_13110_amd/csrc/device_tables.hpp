@@ -170,6 +170,48 @@ struct ResolveArgs {
   int n_batches;
 };
 
+// A register phase of the one-launch kernel: the phases of the whole sweep over
+// a tensor that is one LDS tile, with 2^R (R <= 3) register entries and up to
+// nine thread bits.  off: LDS byte offsets of the register entries (as the poffs
+// of a DevPhase); low / high: those of the thread index's low four and high
+// bits, looked up instead of XORed bit by bit; where the thread bit that
+// controls op 0 is set, with kOneCtl.  (A DUP is the update [1 0; 1 0].)
+constexpr uint32_t kOneCtl = 1u << 31;
+struct OnePhase {
+  uint32_t off[8];
+  uint32_t low[16];
+  uint32_t high[32];
+  int32_t n_ops;
+  int32_t pad[3];
+};
+static_assert(sizeof(OnePhase) == 240, "OnePhase layout");
+
+// The update at (phase, slot): R slots per phase, op = -1 past its updates.
+struct OneSlot {
+  int32_t op;
+  int16_t xrow0, xrow1;
+};
+
+// Launch parameters of the one-launch kernel: the whole amplitude call of
+// tensors of up to 2^12 entries, one batch per block.
+struct OneArgs {
+  const OnePhase* phases;
+  const OneSlot* slots;
+  const float* mats;     // as in ResolveArgs
+  const double2* seg;    // v[2], f[2][2], dot[2][2], then the build-up segments (InitArgs::seg)
+  const double2* J;      // join matrix [vars][K][N]
+  const LateOpDev* prog;
+  const uint8_t* bits;
+  double2* out;          // 2^k amplitudes per batch
+  int n_phases;
+  int n_batches, n, k;
+  int h, m0;
+  int M, K, N, xrow;     // the join, as in LateArgs
+  int join_final;        // the join writes the amplitudes
+  int n_prog, s, j;      // the rest of the late program: M = 2^j rows
+  int final_kind, final_xrow;
+};
+
 // One boundary update of the unfused complex128 reference sweep (a test
 // path, not the hot loop): the pair along `target` of every index becomes
 // m[var][c] * pair (c = the control bit, var = 2 x[xrow0] + x[xrow1]), or

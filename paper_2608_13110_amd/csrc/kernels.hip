@@ -8,6 +8,7 @@
 //             layers, FP64 accumulation (k_late_mf on FP64 matrix cores,
 //             k_late_dot and k_late_out for narrow products), and k_late_ops,
 //             the rest of the late program
+//  k_one      all of it in one launch for tensors of up to 2^12 entries
 //  k_logxeb   FP64 log-XEB reduction; samplers
 //
 // The kernels of the amplitude path are recorded as launches (Launch, see
@@ -1172,28 +1173,29 @@ __device__ inline int insert_zero(int x, int bit) {
   return ((x - lo) << 1) | lo;
 }
 
-__device__ __attribute__((always_inline)) inline void late_ops_body(const LateOpsArgs& a, double2* st, uint32_t bx,
-                                                                    uint32_t by) {
-  const long long row_out = bx;
-  const int b = by;
-  const int sb = a.s;
-  const int total = 1 << (sb + a.j);
-  const double2* in = a.in + (size_t)b * a.in_batch_stride + ((size_t)row_out << (a.j + sb));
-  for (int i = threadIdx.x; i < total; i += blockDim.x) st[i] = in[i];
-  LateOpDev* prog = reinterpret_cast<LateOpDev*>(st + total);
+// Runs src_prog[0..n_prog) on the 2^j rows of 2^sb entries at st (LDS), the
+// program staged at prog (LDS, room for kLateStage ops); bits: the batch's.
+// Starts with a barrier (after the caller's writes of st, and of the first ops
+// where the caller staged them itself) unless n_prog = 0.
+__device__ inline void late_stage(LateOpDev* prog, const LateOpDev* src, int n) {
+  const int words = min(kLateStage, n) * (int)(sizeof(LateOpDev) / 16);
+  for (int i = threadIdx.x; i < words; i += blockDim.x)
+    reinterpret_cast<uint4*>(prog)[i] = reinterpret_cast<const uint4*>(src)[i];
+}
+
+__device__ __attribute__((always_inline)) inline void late_run(double2* st, LateOpDev* prog, const LateOpDev* src_prog,
+                                                               int n_prog, int sb, int j, const uint8_t* bits,
+                                                               bool staged) {
   int l = 0;
-  for (int o = 0; o < a.n_prog; ++o) {
+  for (int o = 0; o < n_prog; ++o) {
     const int at = o % kLateStage;
     if (at == 0) {  // the next ops of the program (every thread is past the last ones: barrier below)
-      constexpr int kWords = sizeof(LateOpDev) / 16;
-      const int words = min(kLateStage, a.n_prog - o) * kWords;
-      const uint4* src = reinterpret_cast<const uint4*>(a.prog + o);
-      for (int i = threadIdx.x; i < words; i += blockDim.x) reinterpret_cast<uint4*>(prog)[i] = src[i];
+      if (!(staged && o == 0)) late_stage(prog, src_prog + o, n_prog - o);
       __syncthreads();
     }
     const LateOpDev& op = prog[at];
     const int kind = __builtin_amdgcn_readfirstlane(op.kind);
-    const int live = a.j - l;
+    const int live = j - l;
     if (kind == 1) {
       const int items = (1 << live) << (sb - 1);
       for (int w = threadIdx.x; w < items; w += blockDim.x) {
@@ -1225,7 +1227,7 @@ __device__ __attribute__((always_inline)) inline void late_ops_body(const LateOp
       }
     } else if (kind == 3) {
       // an output-bit variant (xrow >= 0) takes the second set of matrices
-      const double2* m = op.m + ((op.xrow >= 0 && (a.bits[(size_t)b * a.n + op.xrow] & 1)) ? 8 : 0);
+      const double2* m = op.m + ((op.xrow >= 0 && (bits[op.xrow] & 1)) ? 8 : 0);
       const int items = (1 << (live - 1)) << (sb - 1);
       for (int w = threadIdx.x; w < items; w += blockDim.x) {
         const int ra = (w >> (sb - 1)) << (l + 1);
@@ -1263,19 +1265,37 @@ __device__ __attribute__((always_inline)) inline void late_ops_body(const LateOp
     }
     __syncthreads();
   }
-  if (a.n_prog == 0) __syncthreads();
-  double2* out = a.out + (size_t)b * a.out_batch_stride;
-  if (a.final_kind == 5) {
-    for (int bb = threadIdx.x; bb < (1 << a.k); bb += blockDim.x) {
+}
+
+// The final contraction, by all threads of the block (past a barrier after
+// the last write of st).
+__device__ __attribute__((always_inline)) inline void late_final(const double2* st, double2* out, int final_kind, int k,
+                                                                 const double2* dot, int x) {
+  if (final_kind == 5) {
+    for (int bb = threadIdx.x; bb < (1 << k); bb += blockDim.x) {
       int t = 0;
-      for (int q = 0; q < a.k; ++q) t |= ((bb >> (a.k - 1 - q)) & 1) << q;
+      for (int q = 0; q < k; ++q) t |= ((bb >> (k - 1 - q)) & 1) << q;
       out[bb] = st[t];
     }
-  } else if (a.final_kind == 4) {
-    if (threadIdx.x == 0) {
-      const int x = a.bits[(size_t)b * a.n + a.final_xrow];
-      out[0] = zfma2(a.dot[x][0], st[0], a.dot[x][1], st[1]);
-    }
+  } else if (threadIdx.x == 0) {
+    out[0] = zfma2(dot[2 * x], st[0], dot[2 * x + 1], st[1]);
+  }
+}
+
+__device__ __attribute__((always_inline)) inline void late_ops_body(const LateOpsArgs& a, double2* st, uint32_t bx,
+                                                                    uint32_t by) {
+  const long long row_out = bx;
+  const int b = by;
+  const int sb = a.s;
+  const int total = 1 << (sb + a.j);
+  const double2* in = a.in + (size_t)b * a.in_batch_stride + ((size_t)row_out << (a.j + sb));
+  for (int i = threadIdx.x; i < total; i += blockDim.x) st[i] = in[i];
+  const uint8_t* bits = a.bits + (size_t)b * a.n;
+  late_run(st, reinterpret_cast<LateOpDev*>(st + total), a.prog, a.n_prog, sb, a.j, bits, false);
+  if (a.n_prog == 0) __syncthreads();
+  double2* out = a.out + (size_t)b * a.out_batch_stride;
+  if (a.final_kind != 0) {
+    late_final(st, out, a.final_kind, a.k, &a.dot[0][0], a.final_kind == 4 ? (int)bits[a.final_xrow] & 1 : 0);
   } else {
     for (int t = threadIdx.x; t < (1 << sb); t += blockDim.x) out[((size_t)row_out << sb) + t] = st[t];
   }
@@ -1305,6 +1325,329 @@ hipError_t record_late_ops(const LateOpsArgs& a, Launch* L) {
   L->gfn = reinterpret_cast<const void*>(&k_late_ops_g);
   set_arg(L, a);
   return set_shape(L, a.rows_out, (unsigned)a.n_batches, (unsigned)threads, lds);
+}
+
+// ---------------------------------------------------------------------------
+// The whole amplitude call in one launch: tensors of up to 2^12 entries, one
+// batch per block, from the row-0 build-up to the amplitudes.  As separate
+// launches such a call is all latency (build-up, variants, a pass of one tile
+// per batch whose phases each wait on cold scalar loads of their matrices, the
+// join, the late program).  Here a block keeps its tensor in LDS, and the
+// phases' offsets and the matrices of the batch's variants are staged in LDS
+// too, kOneChunk phases at a time, so a phase waits on nothing farther than
+// LDS.  Few entries per thread (4, or 8 from 2^11 entries on) put the tensor
+// on all four SIMDs: an update of 2^10 entries costs a wave two pairs.  Every
+// update is the same FP32 arithmetic as in the pass kernel, in the same order.
+// Bound by the chain of phases (0.4 us each at w = 10, of which 0.13 us is the
+// arithmetic), with many batches by LDS.  Before and now, in us: one amplitude
+// at w = 10 432 and 48 (24 qubits), 512 batches at w = 6, k = 3 145 and 17,
+// 1024 batches at w = 12, k = 6 775 and 642, at k = 0 24600 and 359.
+constexpr int kOneChunk = 64;
+
+// Product initialisation of entry i, multiplied in the order of init_body.
+__device__ inline float2 one_init(const double2* c, int h, int m, int x0, uint32_t i) {
+  if (i >> m) return make_float2(0.f, 0.f);
+  const double2* seg = c + 10;  // (v, f, the final contraction's vectors, then the segments)
+  auto sg = [&](int j) { return seg[4 * (j - 1) + 2 * (int)((i >> j) & 1u) + (int)((i >> (j - 1)) & 1u)]; };
+  const double2 f = c[2 + 2 * x0 + (int)((i >> (m - 1)) & 1u)];
+  double2 val = c[i & 1u];
+  if (h < 11) {
+    for (int j = 1; j < m; ++j) val = zmul(val, sg(j));
+    val = zmul(val, f);
+  } else {
+    for (int j = 1; j < m && j <= 5; ++j) val = zmul(val, sg(j));
+    const bool f_var = m - 1 >= 6 && m - 1 <= 10;
+    if (!f_var) val = zmul(val, f);
+    for (int j = 6; j < m; ++j) val = zmul(val, sg(j));
+    if (f_var) val = zmul(val, f);
+  }
+  return make_float2((float)val.x, (float)val.y);
+}
+
+// A staged phase: its table, and at a fixed place of its own the matrices of R
+// updates (so nothing is addressed by what was just read).
+constexpr int kOneLow = 16;
+template <int R>
+struct OneStage {
+  OnePhase P;
+  float mats[16 * R];
+};
+
+// n 16-byte words from memory to LDS, four loads in flight per thread.
+template <class Src, class Dst>
+__device__ __attribute__((always_inline)) inline void stage_words(int n, Src src, Dst dst) {
+  const int tid = threadIdx.x, nt = blockDim.x;
+  for (int i0 = tid; i0 < n; i0 += 4 * nt) {
+    uint4 w[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) w[q] = src(min(i0 + q * nt, n - 1));
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (i0 + q * nt < n) dst(i0 + q * nt) = w[q];
+  }
+}
+
+// What a phase needs besides its entries, in registers: the LDS addresses of
+// the thread's entries and the matrices of up to R updates (op 0's picked by
+// its control, the others for both values of theirs).
+template <int R>
+struct OneRegs {
+  uint32_t off[1 << R];
+  float k[8 + 16 * (R - 1)];
+  int n_ops;
+};
+
+// The thread's part of a phase's LDS addresses (and kOneCtl).
+template <int R>
+__device__ __attribute__((always_inline)) inline uint32_t one_thread(const OneStage<R>* S, uint32_t tt) {
+  return S->P.low[tt & (kOneLow - 1)] ^ S->P.high[tt / kOneLow];
+}
+
+template <int R>
+__device__ __attribute__((always_inline)) inline void one_fetch(const OneStage<R>* S, uint32_t base, uint32_t vb,
+                                                                OneRegs<R>& r) {
+  const float4* m = reinterpret_cast<const float4*>(S->mats);
+  auto get = [](float* dst, const float4 x) {
+    dst[0] = x.x;
+    dst[1] = x.y;
+    dst[2] = x.z;
+    dst[3] = x.w;
+  };
+  get(r.k, m[2 * (vb >> 31)]);
+  get(r.k + 4, m[2 * (vb >> 31) + 1]);
+#pragma unroll
+  for (int q = 0; q < 4 * (R - 1); ++q) get(r.k + 8 + 4 * q, m[4 + q]);
+  const uint32_t at = base ^ (vb & ~kOneCtl);
+#pragma unroll
+  for (int q = 0; q < ((1 << R) + 3) / 4; ++q) {
+    const uint4 w = reinterpret_cast<const uint4*>(S->P.off)[q];
+    const uint32_t o[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (4 * q + e < (1 << R)) r.off[4 * q + e] = at ^ o[e];
+  }
+  r.n_ops = S->P.n_ops;
+}
+
+// (the branches of a phase end in the stores: no values to merge)
+template <int R>
+TNC_HD inline void one_store(const Regs<R>& v, const OneRegs<R>& c) {
+#pragma unroll
+  for (int i = 0; i < (1 << R); ++i) lds_put(nullptr, c.off[i], make_float2(v.x[i], v.y[i]));
+}
+
+template <int R>
+__device__ __attribute__((always_inline)) inline void one_rest(Regs<R> v, const OneRegs<R>& c) {
+  if constexpr (R > 1) {
+    const int n_ops = __builtin_amdgcn_readfirstlane(c.n_ops);
+    if (n_ops == 1) return one_store<R>(v, c);
+    v = op_reg<R, 1, 0>(v, (const float*)(c.k + 8));
+    if constexpr (R > 2) {
+      if (n_ops == 2) return one_store<R>(v, c);
+      v = op_reg<R, 2, 1>(v, (const float*)(c.k + 24));
+    }
+  }
+  one_store<R>(v, c);
+}
+
+// One phase from c, with the next one's registers into n and the thread part
+// of the one after it into vb: their reads go out behind this phase's entries
+// and are used after the barrier at the earliest.
+template <int R>
+__device__ __attribute__((always_inline)) inline void one_step(const OneRegs<R>& c, const OneStage<R>* next,
+                                                               const OneStage<R>* next2, uint32_t base, uint32_t tt,
+                                                               OneRegs<R>& n, uint32_t& vb) {
+  Regs<R> v;
+#pragma unroll
+  for (int i = 0; i < (1 << R); ++i) {
+    const float2 t = lds_get(nullptr, c.off[i]);
+    v.x[i] = t.x;
+    v.y[i] = t.y;
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  one_fetch<R>(next, base, vb, n);
+  vb = one_thread<R>(next2, tt);
+  __builtin_amdgcn_sched_barrier(0);
+  v = op_sel<R, 0>(v, (const float*)c.k);
+  // (the addresses are computed here, ahead of the barrier)
+#pragma unroll
+  for (int i = 0; i < (1 << R); ++i) asm volatile("" : "+v"(n.off[i]));
+  asm volatile("" : "+v"(vb));
+  one_rest<R>(v, c);
+}
+
+template <int R>
+__device__ __attribute__((always_inline)) inline void one_body(const OneArgs& a, char* lds, uint32_t bx) {
+  constexpr int E = 1 << R;
+  const int tid = threadIdx.x, nt = blockDim.x;
+  const int h = a.h, TB = h - R;
+  const uint32_t b = bx;
+  const uint8_t* bits = a.bits + (size_t)b * a.n;
+  float2* tile = reinterpret_cast<float2*>(lds);
+  OneStage<R>* phases = reinterpret_cast<OneStage<R>*>(__builtin_assume_aligned(lds + ((size_t)8 << h), 16));
+  const int chunk = min(kOneChunk, max(1, a.n_phases));
+  double2* seg = reinterpret_cast<double2*>(phases + chunk);
+  uint8_t* sbits = reinterpret_cast<uint8_t*>(seg + 10 + 4 * max(0, a.m0 - 1));
+  const uint32_t base = lds_address(lds);
+  // a tile of fewer than 64 threads: the wave's other lanes repeat their work
+  // (the same values to the same addresses, in the same instruction)
+  const uint32_t tt = (uint32_t)tid & ((1u << TB) - 1u);
+  // what does not depend on other loads goes out together
+  for (int i = tid; i < a.n; i += nt) sbits[i] = bits[i];
+  stage_words(10 + 4 * max(0, a.m0 - 1), [&](int i) { return reinterpret_cast<const uint4*>(a.seg)[i]; },
+              [&](int i) -> uint4& { return reinterpret_cast<uint4*>(seg)[i]; });
+  if (a.n_phases == 0) {  // no updates: the build-up alone
+    __syncthreads();
+    for (uint32_t i = tid; i < (1u << h); i += nt) tile[swz(i)] = one_init(seg, h, a.m0, sbits[0], i);
+    __syncthreads();
+  }
+  // a matrix float4 per item, at most kItems per thread and chunk (nt >= 64,
+  // and 256 or more for R = 3)
+  constexpr int kItems = kOneChunk * 4 * R / (R > 2 ? 256 : 64);
+  for (int c = 0; c < a.n_phases; c += kOneChunk) {
+    const int np = min(kOneChunk, a.n_phases - c);
+    if (c > 0) __syncthreads();  // every thread is past the last chunk's phases
+    constexpr int kHead = sizeof(OnePhase) / 16, kStage = sizeof(OneStage<R>) / 16;
+    OneSlot sl[kItems];
+#pragma unroll
+    for (int q = 0; q < kItems; ++q)
+      sl[q] = a.slots[(size_t)c * R + (min(tid + q * nt, np * R * 4 - 1) >> 2)];
+    stage_words(np * kHead, [&](int i) { return reinterpret_cast<const uint4*>(a.phases + c)[i]; },
+                [&](int i) -> uint4& { return reinterpret_cast<uint4*>(phases)[i / kHead * kStage + i % kHead]; });
+    if (c == 0) __syncthreads();  // the bits are staged
+    float4 w[kItems];
+#pragma unroll
+    for (int q = 0; q < kItems; ++q) {
+      const OneSlot x = sl[q];
+      const int i = min(tid + q * nt, np * R * 4 - 1);
+      const int b0 = sbits[max((int)x.xrow0, 0)] & 1, b1 = sbits[max((int)x.xrow1, 0)] & 1;
+      const int var = (x.xrow0 >= 0 ? 2 * b0 : 0) + (x.xrow1 >= 0 ? b1 : 0);
+      w[q] = reinterpret_cast<const float4*>(a.mats + ((size_t)max(x.op, 0) * 4 + var) * 16)[i & 3];
+    }
+    // (the build-up while the matrices arrive)
+    if (c == 0)
+      for (uint32_t i = tid; i < (1u << h); i += nt) tile[swz(i)] = one_init(seg, h, a.m0, sbits[0], i);
+#pragma unroll
+    for (int q = 0; q < kItems; ++q) {
+      const int i = min(tid + q * nt, np * R * 4 - 1);  // (past the end: the last one again, no branch)
+      reinterpret_cast<float4*>(phases[i / (4 * R)].mats)[i % (4 * R)] = w[q];
+    }
+    __syncthreads();
+    // Phase p + 1's offsets and matrices are read while phase p computes: its
+    // entries are then the only thing a phase waits for.  Two phases per turn,
+    // so the two register sets take turns without copies.
+    OneRegs<R> c0, c1;
+    one_fetch<R>(phases, base, one_thread<R>(phases, tt), c0);
+    uint32_t vb = one_thread<R>(phases + min(1, np - 1), tt);
+    for (int p = 0; p < np; p += 2) {
+      one_step<R>(c0, phases + min(p + 1, np - 1), phases + min(p + 2, np - 1), base, tt, c1, vb);
+      __syncthreads();
+      if (p + 1 < np) {
+        one_step<R>(c1, phases + min(p + 2, np - 1), phases + min(p + 3, np - 1), base, tt, c0, vb);
+        __syncthreads();
+      }
+    }
+  }
+  // the late program, past the tile and past the states that replace it
+  LateOpDev* prog = reinterpret_cast<LateOpDev*>(lds + max((size_t)a.M * a.N * 16, (size_t)8 << h));
+  // The join, out[r][c] = sum_kk tile[r K + kk] J[kk][c] in FP64, into
+  // registers first: the states then take the tile's place.  Fewer outputs
+  // than threads: `part` neighbouring threads share an output's K.
+  const int outs = a.M * a.N;
+  int part = 1;
+  while (outs * part * 2 <= nt && part * 2 <= a.K) part *= 2;
+  // (with `part` above 64 the sums meet where the program would go)
+  if (!a.join_final && part <= 64) late_stage(prog, a.prog, a.n_prog);
+  const int var = a.xrow >= 0 ? (int)(bits[a.xrow] & 1) : 0;
+  const double2* __restrict__ J = a.J + (size_t)var * a.K * a.N;
+  double2 acc[E];
+#pragma unroll
+  for (int q = 0; q < E; ++q) {
+    acc[q] = make_double2(0.0, 0.0);
+    const int o = (tid + q * nt) / part, p = tid & (part - 1);
+    if (o < outs) {
+      const int row = o / a.N, col = o % a.N;
+#pragma unroll 4
+      for (int kk = p; kk < a.K; kk += part) {
+        const double2 x = to_d2(tile[swz((uint32_t)(row * a.K + kk))]);
+        const double2 z = J[(size_t)kk * a.N + col];
+        acc[q].x += x.x * z.x - x.y * z.y;
+        acc[q].y += x.x * z.y + x.y * z.x;
+      }
+    }
+    for (int m = 1; m < min(part, 64); m <<= 1) {
+      acc[q].x += __shfl_xor(acc[q].x, m);
+      acc[q].y += __shfl_xor(acc[q].y, m);
+    }
+  }
+  if (part > 64) {  // the waves of an output meet in the staging area
+    double2* red = reinterpret_cast<double2*>(phases);
+    if ((tid & 63) == 0) red[tid >> 6] = acc[0];
+    __syncthreads();
+    if ((tid & (part - 1)) == 0)
+      for (int w = 1; w < part / 64; ++w) {
+        acc[0].x += red[(tid >> 6) + w].x;
+        acc[0].y += red[(tid >> 6) + w].y;
+      }
+  }
+  double2* out = a.out + ((size_t)b << a.k);
+  double2* st = reinterpret_cast<double2*>(lds);
+  if (!a.join_final) __syncthreads();
+#pragma unroll
+  for (int q = 0; q < E; ++q) {
+    const int o = (tid + q * nt) / part;
+    if (o < outs && (tid & (part - 1)) == 0) (a.join_final ? out : st)[o] = acc[q];
+  }
+  if (a.join_final) return;
+  late_run(st, prog, a.prog, a.n_prog, a.s, a.j, bits, part <= 64);
+  if (a.n_prog == 0) __syncthreads();
+  late_final(st, out, a.final_kind, a.k, a.seg + 6, a.final_kind == 4 ? (int)bits[a.final_xrow] & 1 : 0);
+}
+
+template <int R>
+__global__ __launch_bounds__(512) void k_one(OneArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char one_lds[];
+  one_body<R>(a, one_lds, blockIdx.x);
+}
+
+template <int R>
+__global__ __launch_bounds__(512) void k_one_g(const Seg<OneArgs>* __restrict__ segs) {
+  extern __shared__ __attribute__((aligned(16))) char one_lds[];
+  const Seg<OneArgs>* s = group_seg(segs);
+  if (!s) return;
+  const OneArgs a = s->a;
+  one_body<R>(a, one_lds, blockIdx.x);
+}
+
+template <int R>
+static void pick_one(Launch* L) {
+  L->fn = reinterpret_cast<const void*>(&k_one<R>);
+  L->gfn = reinterpret_cast<const void*>(&k_one_g<R>);
+}
+
+hipError_t record_one(const OneArgs& a, Launch* L) {
+  *L = Launch();
+  L->cls = 1;
+  const int R = one_reg_bits(a.h);
+  if (R == 0 || a.n_batches < 1 || a.n_prog < 0 || a.M < 1 || a.K < 1 || a.N < 1 ||
+      (long long)a.M * a.K > (1ll << a.h) || (!a.join_final && a.M * a.N != 1 << (a.j + a.s)))
+    return hipErrorInvalidValue;
+  const int nt = std::max(64, 1 << (a.h - R));
+  if ((long long)a.M * a.N > (long long)nt << R) return hipErrorInvalidValue;  // 2^R outputs per thread
+  if (R == 1) pick_one<1>(L);
+  else if (R == 2) pick_one<2>(L);
+  else pick_one<3>(L);
+  if (a.n < 1 || a.n > 1 << 13) return hipErrorInvalidValue;  // the bits are staged
+  if (R == 3 && nt < 256) return hipErrorInvalidValue;
+  // the tile, a chunk of phases (the waves' partial sums of the join take their
+  // place), the build-up's factors, the bits
+  const size_t stage = R == 1 ? sizeof(OneStage<1>) : R == 2 ? sizeof(OneStage<2>) : sizeof(OneStage<3>);
+  const size_t sweep = ((size_t)8 << a.h) + std::min(kOneChunk, std::max(1, a.n_phases)) * stage +
+                       16 * (size_t)(10 + 4 * std::max(0, a.m0 - 1)) + ((size_t)a.n + 15) / 16 * 16;
+  const size_t late = a.join_final ? 0 : std::max((size_t)a.M * a.N * 16, (size_t)8 << a.h) +
+                                             sizeof(LateOpDev) * (size_t)std::min(kLateStage, a.n_prog);
+  set_arg(L, a);
+  return set_shape(L, a.n_batches, 1, (unsigned)nt, std::max(sweep, late));
 }
 
 // ---------------------------------------------------------------------------

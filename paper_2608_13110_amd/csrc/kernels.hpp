@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 
@@ -137,8 +138,8 @@ __device__ __attribute__((always_inline)) inline void lds_put(char*, uint32_t of
   *(__attribute__((address_space(3))) uint64_t*)(uintptr_t)off = __builtin_bit_cast(uint64_t, v);
 }
 #else
-inline float2 lds_get(char* base, uint32_t off) { return *reinterpret_cast<const float2*>(base + off); }
-inline void lds_put(char* base, uint32_t off, float2 v) { *reinterpret_cast<float2*>(base + off) = v; }
+TNC_HD inline float2 lds_get(char* base, uint32_t off) { return *reinterpret_cast<const float2*>(base + off); }
+TNC_HD inline void lds_put(char* base, uint32_t off, float2 v) { *reinterpret_cast<float2*>(base + off) = v; }
 #endif
 
 // Register-resident complex64 entries of a thread: separate real and
@@ -150,12 +151,21 @@ struct Regs {
 };
 
 // (b0, b1) <- K (b0, b1) with K = [k0 k1; k2 k3] given as 8 floats (re, im).
+// The fused operations are spelled out, so that every kernel rounds an update
+// alike: left to the compiler, which product of a pair is rounded on its own
+// depended on the code around it.
 template <class P>
 TNC_HD inline void cmat2(P k, float& x0, float& y0, float& x1, float& y1) {
-  const float ox0 = k[0] * x0 - k[1] * y0 + k[2] * x1 - k[3] * y1;
-  const float oy0 = k[0] * y0 + k[1] * x0 + k[2] * y1 + k[3] * x1;
-  const float ox1 = k[4] * x0 - k[5] * y0 + k[6] * x1 - k[7] * y1;
-  const float oy1 = k[4] * y0 + k[5] * x0 + k[6] * y1 + k[7] * x1;
+  auto re = [](float a, float b, float c, float d, float u0, float v0, float u1, float v1) {
+    return __builtin_fmaf(-d, v1, __builtin_fmaf(c, u1, __builtin_fmaf(a, u0, -(b * v0))));
+  };
+  auto im = [](float a, float b, float c, float d, float u0, float v0, float u1, float v1) {
+    return __builtin_fmaf(d, u1, __builtin_fmaf(c, v1, __builtin_fmaf(a, v0, b * u0)));
+  };
+  const float ox0 = re(k[0], k[1], k[2], k[3], x0, y0, x1, y1);
+  const float oy0 = im(k[0], k[1], k[2], k[3], x0, y0, x1, y1);
+  const float ox1 = re(k[4], k[5], k[6], k[7], x0, y0, x1, y1);
+  const float oy1 = im(k[4], k[5], k[6], k[7], x0, y0, x1, y1);
   x0 = ox0;
   y0 = oy0;
   x1 = ox1;
@@ -165,8 +175,8 @@ TNC_HD inline void cmat2(P k, float& x0, float& y0, float& x1, float& y1) {
 // The variants take and return the register set by value: the branches of
 // a dispatch then merge values, never element addresses, so every element
 // stays in a VGPR.
-template <int R, int A, int C>
-TNC_HD inline Regs<R> op_reg(Regs<R> v, const TNC_TBL float* __restrict__ m) {
+template <int R, int A, int C, class P>
+TNC_HD inline Regs<R> op_reg(Regs<R> v, P m) {
 #pragma unroll
   for (int i = 0; i < (1 << R); ++i) {
     if (i & (1 << A)) continue;
@@ -661,6 +671,11 @@ hipError_t record_resolve(const ResolveArgs& a, Launch* L);
 hipError_t record_pass(const PassArgs& a, int R, Launch* L);
 hipError_t record_late(const LateArgs& a, bool in_c64, Launch* L);
 hipError_t record_late_ops(const LateOpsArgs& a, Launch* L);
+// The one-launch kernel: register bits of its phases for a 2^h-entry tensor
+// (0: the tensor is too large for it).
+constexpr int kOneMaxBits = 12;
+inline int one_reg_bits(int h) { return h < 1 || h > kOneMaxBits ? 0 : h == 1 ? 1 : h <= 10 ? std::min(2, h - 1) : 3; }
+hipError_t record_one(const OneArgs& a, Launch* L);
 
 hipError_t issue(const Launch& L, hipStream_t s);
 hipError_t graph_add(const Launch& L, hipGraph_t g, hipGraphNode_t* node, const hipGraphNode_t* dep, size_t n_dep);

@@ -1260,6 +1260,15 @@ int schedule4(Plan& p, Schedule& s, std::string* err) {
 
 }  // namespace
 
+Pass plan_one_tile(const Plan& p, const Schedule& s, int R) {
+  Pass ps;
+  ps.w.win_len = p.h;
+  ps.op_end = int(s.ops.size());
+  ps.R = pass_reg_bits(R, p.h);
+  plan_phases(ps, s.ops, ps.R, false);
+  return ps;
+}
+
 int get_schedule(Plan& p, int k, std::shared_ptr<Schedule>* out, std::string* err) {
   if (k < 0 || k > p.n - 1) return fail(err, kErrDomain, "open legs k must satisfy 0 <= k <= n-1");
   if (k >= 1 && 2 * k > p.d) return fail(err, kErrDomain, "open legs k must satisfy 2k <= d");

@@ -214,6 +214,10 @@ int build_plan(int n, int d, const cd* one_qubit, int n_gate2, const Gate2In* ga
 // The schedule for k open legs (cached in the plan).
 int get_schedule(Plan& p, int k, std::shared_ptr<Schedule>* out, std::string* err);
 
+// The whole sweep as one pass over the single tile [0, p.h), 2^R entries per
+// thread, every update on its own (no fused phases).
+Pass plan_one_tile(const Plan& p, const Schedule& s, int R);
+
 // FP64 host execution of the plan's own tables (planner self-check; the GPU
 // path never calls this).  out: n_batches * 2^k amplitudes.
 int execute_host(Plan& p, int k, int n_batches, const uint8_t* bits, cd* out, std::string* err);

@@ -541,8 +541,12 @@ bool ServerImpl::admit(Slot& s, std::deque<std::shared_ptr<Request>>::iterator i
     ++seen[key];
   }
   std::vector<std::shared_ptr<Request>> members{r};
+  // without a batching window, requests share a launch only when they would
+  // otherwise wait: with a free stream for each they run side by side
+  const size_t free_slots = (size_t)std::count_if(slots.begin(), slots.end(), [](const Slot& x) { return x.reqs.empty(); });
+  const bool gather = opt.group_window_us > 0 || ready.size() > free_slots;
   if (mode == 0 && r->small && r->storage == TNC_STORE_C64 && opt.max_group > 1) {
-    for (auto jt = ready.begin(); jt != ready.end() && (int)members.size() < opt.max_group; ++jt) {
+    for (auto jt = ready.begin(); gather && jt != ready.end() && (int)members.size() < opt.max_group; ++jt) {
       if (jt == it) continue;
       const Request& q = **jt;
       if (q.small && q.storage == TNC_STORE_C64 && q.h == r->h) {
@@ -573,7 +577,10 @@ bool ServerImpl::admit(Slot& s, std::deque<std::shared_ptr<Request>>::iterator i
   }
   if (mode == 1) s.graph->busy = true;
   // take the members off the ready queue (r last: `it` stays valid until then)
-  for (size_t i = 1; i < members.size(); ++i) ready.erase(std::find(ready.begin(), ready.end(), members[i]));
+  for (size_t i = 1; i < members.size(); ++i) {
+    ++seen[GraphKey{members[i]->cp->plan, members[i]->k, members[i]->nb, members[i]->storage}];
+    ready.erase(std::find(ready.begin(), ready.end(), members[i]));
+  }
   ready.erase(std::find(ready.begin(), ready.end(), r));
   s.reqs = members;
   const int64_t t = now_ns();

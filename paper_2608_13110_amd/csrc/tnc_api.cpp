@@ -62,6 +62,11 @@ struct HostTables {
   LatePlan late;
   std::vector<LateOpDev> prog;
   uint64_t bytes_late[2] = {0, 0};
+  // the one-launch kernel's tables (one: the schedule takes it)
+  bool one = false;
+  std::vector<OnePhase> one_phases;
+  std::vector<OneSlot> one_slots;
+  std::vector<double2> one_seg;
 };
 
 // FP32 form of an update matrix K (FP64), 8 floats (re, im) row-major.
@@ -167,6 +172,73 @@ void fused_operand(const float* U32, float4* lanes) {
   }
 }
 
+// The tables of the one-launch kernel, where the call takes it: a tensor that
+// is one LDS tile of the kernel, updates on their own (fused products round
+// differently and stay on the pass kernel), and a join small enough for one
+// block (2^(h + k) FP64 products: 2^18 take it 7 us; above, the join's own
+// kernels spread them over the chip).
+void build_one(const Plan& p, const Schedule& s, HostTables* t) {
+  const int R = one_reg_bits(p.h), h = p.h;
+  if (p.chi != 2 || R == 0 || h + s.k > 18) return;
+  for (const Pass& ps : s.passes)
+    for (const Phase& ph : ps.phases)
+      if (ph.mf != 0) return;
+  const Pass ps = plan_one_tile(p, s, R);
+  if (ps.R != R) return;
+  for (const Phase& ph : ps.phases) {
+    const int n_ops = ph.op_end - ph.op_begin;
+    if (ph.mf != 0 || n_ops < 1 || n_ops > R) return;
+    OnePhase o;
+    std::memset(&o, 0, sizeof(o));
+    o.n_ops = n_ops;
+    const SweepOp& first = s.ops[ph.op_begin];
+    const int ctl = first.kind == OP_CU ? first.control : -1;
+    bool ctl_found = ctl < 0;
+    uint32_t seen = 0;
+    for (int b = 0; b < R; ++b) {
+      if (ph.reg[b] < 0 || ph.reg[b] >= h || (seen >> ph.reg[b] & 1u)) return;
+      seen |= 1u << ph.reg[b];
+    }
+    for (int i = 0; i < (1 << R); ++i) {
+      uint32_t r = 0;
+      for (int b = 0; b < R; ++b)
+        if (i >> b & 1) r |= 1u << ph.reg[b];
+      o.off[i] = swz(r) << 3;
+    }
+    for (int q = 0; q < h - R; ++q) {
+      if (ph.tpos[q] < 0 || ph.tpos[q] >= h || (seen >> ph.tpos[q] & 1u)) return;
+      seen |= 1u << ph.tpos[q];
+      const uint32_t w = (swz(1u << ph.tpos[q]) << 3) | (ph.tpos[q] == ctl ? kOneCtl : 0u);
+      for (int i = 0; i < (q < 4 ? 16 : 32); ++i)
+        if (i >> (q < 4 ? q : q - 4) & 1) (q < 4 ? o.low : o.high)[i] ^= w;
+      ctl_found = ctl_found || ph.tpos[q] == ctl;
+    }
+    for (int b = 0; b < n_ops; ++b) {
+      const SweepOp& op = s.ops[ph.op_begin + b];
+      if ((op.kind != OP_CU && (b > 0 || op.kind != OP_DUP)) || op.target != ph.reg[b]) return;
+      if (b > 0 && op.control != ph.reg[b - 1]) return;
+    }
+    if (!ctl_found) return;
+    t->one_phases.push_back(o);
+    for (int b = 0; b < R; ++b) {
+      OneSlot sl{-1, -1, -1};
+      if (b < n_ops) {
+        sl.op = ph.op_begin + b;
+        sl.xrow0 = (int16_t)s.ops[sl.op].xrow[0];
+        sl.xrow1 = (int16_t)s.ops[sl.op].xrow[1];
+      }
+      t->one_slots.push_back(sl);
+    }
+  }
+  auto d2 = [](cd z) { return make_double2(z.real(), z.imag()); };
+  for (int w = 0; w < 2; ++w) t->one_seg.push_back(d2(p.init_v[w]));
+  for (int x = 0; x < 2; ++x)
+    for (int w = 0; w < 2; ++w) t->one_seg.push_back(d2(p.init_f[x][w]));
+  for (int q = 0; q < 4; ++q) t->one_seg.push_back(t->late.final_kind == L_DOT ? d2(t->late.dot[q]) : make_double2(0, 0));
+  t->one_seg.insert(t->one_seg.end(), t->seg.begin(), t->seg.end());
+  t->one = true;
+}
+
 int build_tables(Plan& p, const Schedule& s, HostTables* t, std::string* err) {
   const size_t nops = s.ops.size();
   t->ops.resize(nops);
@@ -257,6 +329,9 @@ int build_tables(Plan& p, const Schedule& s, HostTables* t, std::string* err) {
       }
     if (fused_left > 0) --fused_left;
     else acc += step;
+    if (op.kind == OP_DUP)  // the copy as an update (the one-launch kernel; the pass kernels copy)
+      for (int q = 0; q < 8; ++q)
+        for (int e = 0; e < 8; ++e) t->mats[(o * 4 + q / 2) * 16 + (q & 1) * 8 + e] = e == 0 || e == 4 ? 1.f : 0.f;
   }
   for (const Pass& ps : s.passes) {
     PassHost ph;
@@ -507,6 +582,7 @@ int build_tables(Plan& p, const Schedule& s, HostTables* t, std::string* err) {
     uint64_t& slot = t->bytes_late[(i + 1) & 1];
     slot = std::max(slot, bytes);
   }
+  build_one(p, s, t);
   return 0;
 }
 
@@ -565,6 +641,7 @@ int check_storage(const HostTables& t, int storage) {
 struct DevSched {
   int device = -1;
   HostTables host;
+  char* arena = nullptr;  // all of the following
   DevOp* d_ops = nullptr;
   float* d_mats = nullptr;
   DevPhase* d_phases = nullptr;
@@ -573,6 +650,9 @@ struct DevSched {
   double2* d_seg = nullptr;
   double2* d_J = nullptr;
   LateOpDev* d_prog = nullptr;
+  OnePhase* d_one_phases = nullptr;
+  OneSlot* d_one_slots = nullptr;
+  double2* d_one_seg = nullptr;
   // the complex128 reference sweep's updates (built on its first use)
   std::mutex mu64;
   Op64* d_ops64 = nullptr;
@@ -580,7 +660,7 @@ struct DevSched {
     int prev = 0;
     if (device >= 0 && hipGetDevice(&prev) == hipSuccess) {
       (void)hipSetDevice(device);
-      void* ptrs[] = {d_ops, d_mats, d_phases, d_poffs, d_fmats, d_seg, d_J, d_prog, d_ops64};
+      void* ptrs[] = {arena, d_ops64};
       for (void* q : ptrs)
         if (q) (void)hipFree(q);
       (void)hipSetDevice(prev);
@@ -614,6 +694,28 @@ int upload(T** dst, const std::vector<T>& src) {
   return 0;
 }
 
+// Tables that go up together: one allocation and one copy (an allocation and
+// a copy of their own cost each table about 20 us, eleven tables per call
+// shape).
+struct TableUpload {
+  std::vector<std::pair<void**, uint64_t>> at;
+  std::vector<char> bytes;
+  template <typename T>
+  void add(T** dst, const std::vector<T>& src) {
+    if (src.empty()) return;
+    bytes.resize(align256(bytes.size()));
+    at.push_back({reinterpret_cast<void**>(dst), bytes.size()});
+    const char* p = reinterpret_cast<const char*>(src.data());
+    bytes.insert(bytes.end(), p, p + src.size() * sizeof(T));
+  }
+  int run(char** arena) {
+    const int rc = upload(arena, bytes);
+    if (!rc)
+      for (auto& x : at) *x.first = *arena + x.second;
+    return rc;
+  }
+};
+
 int get_dev_sched(Plan& p, int k, std::shared_ptr<DevSched>* out) {
   if (p.h > kMaxDeviceWidth) return set_err(TNC_E_DOMAIN, "boundary tensors above 2^40 entries are planned only");
   int dev = 0;
@@ -634,14 +736,20 @@ int get_dev_sched(Plan& p, int k, std::shared_ptr<DevSched>* out) {
   ds->device = dev;
   rc = build_tables(p, *s, &ds->host, &err);
   if (rc) return set_err(rc, err);
-  std::vector<double2> J;
-  for (const cd& z : ds->host.late.first.J) J.push_back(make_double2(z.real(), z.imag()));
-  if ((rc = upload(&ds->d_ops, ds->host.ops)) || (rc = upload(&ds->d_mats, ds->host.mats)) ||
-      (rc = upload(&ds->d_phases, ds->host.phases)) || (rc = upload(&ds->d_poffs, ds->host.poffs)) ||
-      (rc = upload(&ds->d_fmats, ds->host.fmats)) ||
-      (rc = upload(&ds->d_seg, ds->host.seg)) ||
-      (rc = upload(&ds->d_J, J)) || (rc = upload(&ds->d_prog, ds->host.prog)))
-    return rc;
+  TableUpload up;
+  up.add(&ds->d_ops, ds->host.ops);
+  up.add(&ds->d_mats, ds->host.mats);
+  up.add(&ds->d_phases, ds->host.phases);
+  up.add(&ds->d_poffs, ds->host.poffs);
+  up.add(&ds->d_fmats, ds->host.fmats);
+  up.add(&ds->d_seg, ds->host.seg);
+  static_assert(sizeof(cd) == sizeof(double2), "(re, im)");
+  up.add(reinterpret_cast<cd**>(&ds->d_J), ds->host.late.first.J);
+  up.add(&ds->d_prog, ds->host.prog);
+  up.add(&ds->d_one_phases, ds->host.one_phases);
+  up.add(&ds->d_one_slots, ds->host.one_slots);
+  up.add(&ds->d_one_seg, ds->host.one_seg);
+  if ((rc = up.run(&ds->arena))) return rc;
   pd.m[{k, dev}] = ds;
   *out = ds;
   return 0;
@@ -815,6 +923,41 @@ LateOpsArgs ops_args(const Plan& p, const HostTables& t, const LateOpsLaunch& ln
   return a;
 }
 
+OneArgs one_args(const Plan& p, const DevSched& ds, int nb, const uint8_t* bits, int k, double2* out) {
+  const HostTables& t = ds.host;
+  const LateFirst& F = t.late.first;
+  OneArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.phases = ds.d_one_phases;
+  a.slots = ds.d_one_slots;
+  a.mats = ds.d_mats;
+  a.seg = ds.d_one_seg;
+  a.J = ds.d_J;
+  a.prog = ds.d_prog;
+  a.bits = bits;
+  a.out = out;
+  a.n_phases = (int)t.one_phases.size();
+  a.n_batches = nb;
+  a.n = p.n;
+  a.k = k;
+  a.h = p.h;
+  a.m0 = p.m0;
+  a.M = (int)F.M;
+  a.K = F.K;
+  a.N = F.N;
+  a.xrow = F.xrow;
+  a.join_final = F.final ? 1 : 0;
+  a.s = t.late.s;
+  a.final_kind = t.late.final_kind;
+  a.final_xrow = t.late.final_xrow;
+  if (!F.final) {
+    a.prog += t.late.ops.front().op_begin;
+    a.n_prog = t.late.ops.back().op_end - t.late.ops.front().op_begin;
+    for (const LateOpsLaunch& ln : t.late.ops) a.j += ln.j;
+  }
+  return a;
+}
+
 // Every launch of one amplitude call, in order, recorded with its arguments:
 // for each group of batches that fits the workspace, the row-0 build-up, the
 // variant resolution, the passes, the join and the late launches.
@@ -836,6 +979,12 @@ int record_launches(Plan& p, DevSched& ds, int nb_total, const uint8_t* d_bits, 
   };
   out->clear();
   Launch rec;
+  if (t.one && !s16) {
+    const OneArgs a = one_args(p, ds, nb_total, d_bits, k, reinterpret_cast<double2*>(d_out));
+    if (record_one(a, &rec) != hipSuccess) return shape_err("one launch");
+    out->push_back(rec);
+    return TNC_OK;
+  }
   for (int b0 = 0; b0 < nb_total; b0 += chunk) {
     const int nb = std::min(chunk, nb_total - b0);
     char* q = base;
