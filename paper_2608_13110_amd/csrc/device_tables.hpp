@@ -192,6 +192,22 @@ struct OneSlot {
   int16_t xrow0, xrow1;
 };
 
+// Launch parameters of a pass of the latency kernel: the pass over a window of
+// a tensor too small to fill the chip, one 2^T-entry tile per block.
+struct WinArgs {
+  const OnePhase* phases;
+  const OneSlot* slots;
+  const float* mats;
+  const double2* seg;    // as in OneArgs (init only)
+  const uint8_t* bits;
+  float2* B;
+  int n_phases;
+  int n, h, m0;
+  int T, lo_bits, win_lo, win_len;
+  int n_tiles;           // batches << (h - T)
+  int init;              // the first pass: the build-up in place of a read
+};
+
 // Launch parameters of the one-launch kernel: the whole amplitude call of
 // tensors of up to 2^12 entries, one batch per block.
 struct OneArgs {

@@ -17,6 +17,10 @@ namespace tnc {
 int record_amplitudes(tnc_plan_t plan, int32_t n_batches, const uint8_t* d_bits, int32_t k, int32_t storage,
                       tnc_c128* d_out, void* d_workspace, uint64_t workspace_bytes, std::vector<Launch>* out);
 
+// At most the launches that record_amplitudes records for one group of batches
+// (all of them, given the whole workspace), from the plan alone.
+int max_launches(tnc_plan_t plan, int32_t k, uint64_t* count);
+
 // Issues recorded launches in order on `stream` (timed while profiling is
 // on); TNC_E_DEVICE with the failing launch's own status.
 int issue_recorded(const std::vector<Launch>& ls, hipStream_t stream);

@@ -9,6 +9,7 @@
 //             k_late_dot and k_late_out for narrow products), and k_late_ops,
 //             the rest of the late program
 //  k_one      all of it in one launch for tensors of up to 2^12 entries
+//  k_win      the pass over tensors too small to fill the chip
 //  k_logxeb   FP64 log-XEB reduction; samplers
 //
 // The kernels of the amplitude path are recorded as launches (Launch, see
@@ -1356,9 +1357,10 @@ __device__ inline float2 one_init(const double2* c, int h, int m, int x0, uint32
     val = zmul(val, f);
   } else {
     for (int j = 1; j < m && j <= 5; ++j) val = zmul(val, sg(j));
+    for (int j = 12; j < m; ++j) val = zmul(val, sg(j));
     const bool f_var = m - 1 >= 6 && m - 1 <= 10;
     if (!f_var) val = zmul(val, f);
-    for (int j = 6; j < m; ++j) val = zmul(val, sg(j));
+    for (int j = 6; j < m && j <= 11; ++j) val = zmul(val, sg(j));
     if (f_var) val = zmul(val, f);
   }
   return make_float2((float)val.x, (float)val.y);
@@ -1476,43 +1478,34 @@ __device__ __attribute__((always_inline)) inline void one_step(const OneRegs<R>&
   one_rest<R>(v, c);
 }
 
-template <int R>
-__device__ __attribute__((always_inline)) inline void one_body(const OneArgs& a, char* lds, uint32_t bx) {
-  constexpr int E = 1 << R;
+// The phases of a tile in LDS (at address `base`): tables and matrices staged at
+// `stage`, kOneChunk phases at a time; sbits: the batch's bits in LDS (written by
+// the caller, no barrier since).  fill() writes the tile; it runs once, behind
+// the first chunk's loads and ahead of the barrier before the first phase.
+// Ends with a barrier.
+template <int R, class Fill>
+__device__ __attribute__((always_inline)) inline void one_sweep(const OnePhase* tables, const OneSlot* slots,
+                                                                const float* all_mats, int n_phases, OneStage<R>* phases,
+                                                                const uint8_t* sbits, uint32_t base, uint32_t tt,
+                                                                Fill fill) {
   const int tid = threadIdx.x, nt = blockDim.x;
-  const int h = a.h, TB = h - R;
-  const uint32_t b = bx;
-  const uint8_t* bits = a.bits + (size_t)b * a.n;
-  float2* tile = reinterpret_cast<float2*>(lds);
-  OneStage<R>* phases = reinterpret_cast<OneStage<R>*>(__builtin_assume_aligned(lds + ((size_t)8 << h), 16));
-  const int chunk = min(kOneChunk, max(1, a.n_phases));
-  double2* seg = reinterpret_cast<double2*>(phases + chunk);
-  uint8_t* sbits = reinterpret_cast<uint8_t*>(seg + 10 + 4 * max(0, a.m0 - 1));
-  const uint32_t base = lds_address(lds);
-  // a tile of fewer than 64 threads: the wave's other lanes repeat their work
-  // (the same values to the same addresses, in the same instruction)
-  const uint32_t tt = (uint32_t)tid & ((1u << TB) - 1u);
-  // what does not depend on other loads goes out together
-  for (int i = tid; i < a.n; i += nt) sbits[i] = bits[i];
-  stage_words(10 + 4 * max(0, a.m0 - 1), [&](int i) { return reinterpret_cast<const uint4*>(a.seg)[i]; },
-              [&](int i) -> uint4& { return reinterpret_cast<uint4*>(seg)[i]; });
-  if (a.n_phases == 0) {  // no updates: the build-up alone
+  if (n_phases == 0) {  // no updates
     __syncthreads();
-    for (uint32_t i = tid; i < (1u << h); i += nt) tile[swz(i)] = one_init(seg, h, a.m0, sbits[0], i);
+    fill();
     __syncthreads();
   }
   // a matrix float4 per item, at most kItems per thread and chunk (nt >= 64,
   // and 256 or more for R = 3)
   constexpr int kItems = kOneChunk * 4 * R / (R > 2 ? 256 : 64);
-  for (int c = 0; c < a.n_phases; c += kOneChunk) {
-    const int np = min(kOneChunk, a.n_phases - c);
+  for (int c = 0; c < n_phases; c += kOneChunk) {
+    const int np = min(kOneChunk, n_phases - c);
     if (c > 0) __syncthreads();  // every thread is past the last chunk's phases
     constexpr int kHead = sizeof(OnePhase) / 16, kStage = sizeof(OneStage<R>) / 16;
     OneSlot sl[kItems];
 #pragma unroll
     for (int q = 0; q < kItems; ++q)
-      sl[q] = a.slots[(size_t)c * R + (min(tid + q * nt, np * R * 4 - 1) >> 2)];
-    stage_words(np * kHead, [&](int i) { return reinterpret_cast<const uint4*>(a.phases + c)[i]; },
+      sl[q] = slots[(size_t)c * R + (min(tid + q * nt, np * R * 4 - 1) >> 2)];
+    stage_words(np * kHead, [&](int i) { return reinterpret_cast<const uint4*>(tables + c)[i]; },
                 [&](int i) -> uint4& { return reinterpret_cast<uint4*>(phases)[i / kHead * kStage + i % kHead]; });
     if (c == 0) __syncthreads();  // the bits are staged
     float4 w[kItems];
@@ -1522,11 +1515,9 @@ __device__ __attribute__((always_inline)) inline void one_body(const OneArgs& a,
       const int i = min(tid + q * nt, np * R * 4 - 1);
       const int b0 = sbits[max((int)x.xrow0, 0)] & 1, b1 = sbits[max((int)x.xrow1, 0)] & 1;
       const int var = (x.xrow0 >= 0 ? 2 * b0 : 0) + (x.xrow1 >= 0 ? b1 : 0);
-      w[q] = reinterpret_cast<const float4*>(a.mats + ((size_t)max(x.op, 0) * 4 + var) * 16)[i & 3];
+      w[q] = reinterpret_cast<const float4*>(all_mats + ((size_t)max(x.op, 0) * 4 + var) * 16)[i & 3];
     }
-    // (the build-up while the matrices arrive)
-    if (c == 0)
-      for (uint32_t i = tid; i < (1u << h); i += nt) tile[swz(i)] = one_init(seg, h, a.m0, sbits[0], i);
+    if (c == 0) fill();  // (while the matrices arrive)
 #pragma unroll
     for (int q = 0; q < kItems; ++q) {
       const int i = min(tid + q * nt, np * R * 4 - 1);  // (past the end: the last one again, no branch)
@@ -1548,6 +1539,31 @@ __device__ __attribute__((always_inline)) inline void one_body(const OneArgs& a,
       }
     }
   }
+}
+
+template <int R>
+__device__ __attribute__((always_inline)) inline void one_body(const OneArgs& a, char* lds, uint32_t bx) {
+  constexpr int E = 1 << R;
+  const int tid = threadIdx.x, nt = blockDim.x;
+  const int h = a.h, TB = h - R;
+  const uint32_t b = bx;
+  const uint8_t* bits = a.bits + (size_t)b * a.n;
+  float2* tile = reinterpret_cast<float2*>(lds);
+  OneStage<R>* phases = reinterpret_cast<OneStage<R>*>(__builtin_assume_aligned(lds + ((size_t)8 << h), 16));
+  const int chunk = min(kOneChunk, max(1, a.n_phases));
+  double2* seg = reinterpret_cast<double2*>(phases + chunk);
+  uint8_t* sbits = reinterpret_cast<uint8_t*>(seg + 10 + 4 * max(0, a.m0 - 1));
+  const uint32_t base = lds_address(lds);
+  // a tile of fewer than 64 threads: the wave's other lanes repeat their work
+  // (the same values to the same addresses, in the same instruction)
+  const uint32_t tt = (uint32_t)tid & ((1u << TB) - 1u);
+  // what does not depend on other loads goes out together
+  for (int i = tid; i < a.n; i += nt) sbits[i] = bits[i];
+  stage_words(10 + 4 * max(0, a.m0 - 1), [&](int i) { return reinterpret_cast<const uint4*>(a.seg)[i]; },
+              [&](int i) -> uint4& { return reinterpret_cast<uint4*>(seg)[i]; });
+  one_sweep<R>(a.phases, a.slots, a.mats, a.n_phases, phases, sbits, base, tt, [&]() {
+    for (uint32_t i = tid; i < (1u << h); i += nt) tile[swz(i)] = one_init(seg, h, a.m0, sbits[0], i);
+  });
   // the late program, past the tile and past the states that replace it
   LateOpDev* prog = reinterpret_cast<LateOpDev*>(lds + max((size_t)a.M * a.N * 16, (size_t)8 << h));
   // The join, out[r][c] = sum_kk tile[r K + kk] J[kk][c] in FP64, into
@@ -1648,6 +1664,105 @@ hipError_t record_one(const OneArgs& a, Launch* L) {
                                              sizeof(LateOpDev) * (size_t)std::min(kLateStage, a.n_prog);
   set_arg(L, a);
   return set_shape(L, a.n_batches, 1, (unsigned)nt, std::max(sweep, late));
+}
+
+// ---------------------------------------------------------------------------
+// One pass over a window of a tensor too small to fill the chip (2^13 to 2^20
+// entries in all): bound by latency, launch after launch, so the tiles are the
+// smallest that still cover the slots with two windows (most CUs, fewest
+// entries per thread) and the phases run from LDS as in the one-launch kernel.
+// The pass kernel's phases wait on two scalar loads each, cold in every launch.
+// The first pass builds its tile up instead of reading it.
+// One pass at w = 17, one batch: 7.6 us (36 of them, 128 tiles of 2^10 entries)
+// against 17 us on average (16 tiles of 2^13); a call of 41 qubits, k = 5, 782
+// us before and 318 us now.
+template <int R>
+__device__ __attribute__((always_inline)) inline void win_body(const WinArgs& a, char* lds, uint32_t bx) {
+  constexpr int E = 1 << R;
+  const int tid = threadIdx.x, nt = blockDim.x;
+  const int T = a.T, TB = T - R;
+  const int tbits = a.h - T;
+  const uint32_t tile = xcd_block(bx, (uint32_t)a.n_tiles);
+  const uint32_t b = tile >> tbits;
+  const uint64_t boff = block_offset(tile & ((1u << tbits) - 1u), a.lo_bits, a.win_lo, a.win_len);
+  const uint8_t* bits = a.bits + (size_t)b * a.n;
+  float2* __restrict__ B = a.B + ((size_t)b << a.h) + boff;
+  OneStage<R>* phases = reinterpret_cast<OneStage<R>*>(__builtin_assume_aligned(lds + ((size_t)8 << T), 16));
+  double2* seg = reinterpret_cast<double2*>(phases + min(kOneChunk, max(1, a.n_phases)));
+  const int n_seg = 10 + 4 * max(0, a.m0 - 1);
+  uint8_t* sbits = reinterpret_cast<uint8_t*>(seg + (a.init ? n_seg : 0));
+  const uint32_t tt = (uint32_t)tid & ((1u << TB) - 1u);
+  // entry pairs it * 2^(TB + 1) + 2 tt of the tile (HBM order), all loads first
+  const uint32_t st = swz(tt * 2u);
+  const IterSlots isl(TB + 1);
+  float4 ld[E / 2];
+  if (!a.init) {
+#pragma unroll
+    for (int it = 0; it < E / 2; ++it)
+      ld[it] = *reinterpret_cast<const float4*>(B + tile_offset(((uint32_t)it << (TB + 1)) + tt * 2u, a.lo_bits, a.win_lo));
+  }
+  for (int i = tid; i < a.n; i += nt) sbits[i] = bits[i];
+  if (a.init)
+    stage_words(n_seg, [&](int i) { return reinterpret_cast<const uint4*>(a.seg)[i]; },
+                [&](int i) -> uint4& { return reinterpret_cast<uint4*>(seg)[i]; });
+  one_sweep<R>(a.phases, a.slots, a.mats, a.n_phases, phases, sbits, lds_address(lds), tt, [&]() {
+    if (a.init) {
+      float2* t = reinterpret_cast<float2*>(lds);
+      for (uint32_t i = tid; i < (1u << T); i += nt)
+        t[swz(i)] = one_init(seg, a.h, a.m0, sbits[0], (uint32_t)(boff + tile_offset(i, a.lo_bits, a.win_lo)));
+    } else {
+#pragma unroll
+      for (int it = 0; it < E / 2; ++it) {
+        const uint32_t si = isl.of(it) ^ st;
+        *reinterpret_cast<float4*>(lds + pair_slot(si)) = pair_order(ld[it], pair_swapped(si));
+      }
+    }
+  });
+#pragma unroll
+  for (int it = 0; it < E / 2; ++it) {
+    const uint32_t si = isl.of(it) ^ st;
+    const float4 v = *reinterpret_cast<const float4*>(lds + pair_slot(si));
+    *reinterpret_cast<float4*>(B + tile_offset(((uint32_t)it << (TB + 1)) + tt * 2u, a.lo_bits, a.win_lo)) =
+        pair_order(v, pair_swapped(si));
+  }
+}
+
+template <int R>
+__global__ __launch_bounds__(512) void k_win(WinArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char one_lds[];
+  win_body<R>(a, one_lds, blockIdx.x);
+}
+
+template <int R>
+__global__ __launch_bounds__(512) void k_win_g(const Seg<WinArgs>* __restrict__ segs) {
+  extern __shared__ __attribute__((aligned(16))) char one_lds[];
+  const Seg<WinArgs>* s = group_seg(segs);
+  if (!s) return;
+  const WinArgs a = s->a;
+  win_body<R>(a, one_lds, blockIdx.x);
+}
+
+hipError_t record_win(const WinArgs& a, int R, Launch* L) {
+  *L = Launch();
+  L->cls = 1;
+  const int TB = a.T - R;
+  // one thread per 2^R entries, whole waves; pairs of entries in the low slots
+  if ((R != 2 && R != 3) || TB < 6 || TB > 9 || (R == 3 && TB < 8) || a.T > a.h || a.h > 31 || a.n_tiles < 1 ||
+      a.lo_bits + a.win_len != a.T || (a.lo_bits < 1 && a.win_lo != 0) || a.win_lo < a.lo_bits ||
+      a.win_lo + a.win_len > a.h || a.n < 1 || a.n > 1 << 13)
+    return hipErrorInvalidValue;
+  if (R == 2) {
+    L->fn = reinterpret_cast<const void*>(&k_win<2>);
+    L->gfn = reinterpret_cast<const void*>(&k_win_g<2>);
+  } else {
+    L->fn = reinterpret_cast<const void*>(&k_win<3>);
+    L->gfn = reinterpret_cast<const void*>(&k_win_g<3>);
+  }
+  const size_t stage = R == 2 ? sizeof(OneStage<2>) : sizeof(OneStage<3>);
+  const size_t lds = ((size_t)8 << a.T) + std::min(kOneChunk, std::max(1, a.n_phases)) * stage +
+                     (a.init ? 16 * (size_t)(10 + 4 * std::max(0, a.m0 - 1)) : 0) + ((size_t)a.n + 15) / 16 * 16;
+  set_arg(L, a);
+  return set_shape(L, a.n_tiles, 1, 1u << TB, lds);
 }
 
 // ---------------------------------------------------------------------------

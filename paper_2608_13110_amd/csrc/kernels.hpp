@@ -676,6 +676,13 @@ hipError_t record_late_ops(const LateOpsArgs& a, Launch* L);
 constexpr int kOneMaxBits = 12;
 inline int one_reg_bits(int h) { return h < 1 || h > kOneMaxBits ? 0 : h == 1 ? 1 : h <= 10 ? std::min(2, h - 1) : 3; }
 hipError_t record_one(const OneArgs& a, Launch* L);
+// The latency kernel's tiles for a 2^h-entry tensor (13 <= h <= 20): the
+// smallest that cover the slots with two windows, and register bits for them.
+constexpr int kWinMaxBits = 20;
+inline int win_low_bits(int h) { return h % 2 ? 2 : 3; }
+inline int win_tile_bits(int h) { return (h + win_low_bits(h) + 1) / 2; }
+inline int win_reg_bits(int T) { return T <= 10 ? 2 : 3; }
+hipError_t record_win(const WinArgs& a, int R, Launch* L);
 
 hipError_t issue(const Launch& L, hipStream_t s);
 hipError_t graph_add(const Launch& L, hipGraph_t g, hipGraphNode_t* node, const hipGraphNode_t* dep, size_t n_dep);

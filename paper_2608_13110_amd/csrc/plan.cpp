@@ -529,9 +529,9 @@ namespace {
 // d - 1 slots).
 int live_after_row(const Plan& p, int r) { return p.chi == 4 ? p.h : int(p.X[r].size()); }
 
-std::vector<Window> window_grid(const Plan& p, int hmax) {
-  const int T = p.opt.max_tile_bits;
-  const int C = p.opt.low_bits;
+std::vector<Window> window_grid(const Options& opt, int hmax) {
+  const int T = opt.max_tile_bits;
+  const int C = opt.low_bits;
   std::vector<Window> ws;
   if (hmax <= T) {
     Window w;
@@ -603,7 +603,7 @@ std::vector<Window> window_grid_overlap(const Plan& p, int hmax, int ov) {
   if (hmax <= T) return ws;
   const int L = T - C;
   const int S = T - ov, E = hmax - 1;
-  if (L <= ov) return window_grid(p, hmax);
+  if (L <= ov) return window_grid(p.opt, hmax);
   const int m = std::max(1, (E - S + 1 - ov + (L - ov) - 1) / (L - ov));
   const int last = E - L + 1;
   for (int k = 0; k < m; ++k) {
@@ -612,7 +612,7 @@ std::vector<Window> window_grid_overlap(const Plan& p, int hmax, int ov) {
     x.win_lo = m == 1 ? std::max(S, last) : S + (int)std::lround((double)(last - S) * k / (m - 1));
     x.win_len = std::min(L, hmax - x.win_lo);
     if (x.win_lo < C) {  // would overlap the low slots: fall back
-      return window_grid(p, hmax);
+      return window_grid(p.opt, hmax);
     }
     ws.push_back(x);
   }
@@ -989,10 +989,10 @@ void split_triples(Pass& ps, const std::vector<SweepOp>& ops) {
   }
 }
 
-std::vector<Pass> plan_passes(const Plan& p, const std::vector<SweepOp>& ops, int R) {
+std::vector<Pass> plan_passes(const Plan& p, const Options& opt, const std::vector<SweepOp>& ops, int R) {
   std::vector<Pass> passes;
   if (ops.empty()) return passes;
-  auto ws = p.chi == 4 && !p.spatial ? window_grid_overlap(p, p.h, 2) : window_grid(p, p.h);
+  auto ws = p.chi == 4 && !p.spatial ? window_grid_overlap(p, p.h, 2) : window_grid(opt, p.h);
   int i = 0;
   const int nops = int(ops.size());
   while (i < nops) {
@@ -1009,18 +1009,18 @@ std::vector<Pass> plan_passes(const Plan& p, const std::vector<SweepOp>& ops, in
     ps.op_end = i + best_len;
     const int T = ps.w.tile_bits();
     ps.R = pass_reg_bits(R, T);
-    plan_phases(ps, ops, ps.R, p.opt.math == 2);
+    plan_phases(ps, ops, ps.R, opt.math == 2);
     // Fewer entries per thread leave registers for more resident waves:
     // take one register bit less when the pass needs no more phases with
     // it and a tile still fits one 256-thread block.
-    if (p.opt.reg_adapt == 1 && ps.R >= 3 && T - (ps.R - 1) <= 8) {
+    if (opt.reg_adapt == 1 && ps.R >= 3 && T - (ps.R - 1) <= 8) {
       Pass alt = ps;
       alt.R = ps.R - 1;
       alt.phases.clear();
-      plan_phases(alt, ops, alt.R, p.opt.math == 2);
+      plan_phases(alt, ops, alt.R, opt.math == 2);
       if (alt.phases.size() == ps.phases.size()) ps = alt;
     }
-    if (p.opt.math == 2) split_triples(ps, ops);
+    if (opt.math == 2) split_triples(ps, ops);
     passes.push_back(ps);
     i += best_len;
   }
@@ -1232,7 +1232,7 @@ int schedule4(Plan& p, Schedule& s, std::string* err) {
   }
   // a dense update holds two register bits
   s.reg_bits = std::max(2, std::min(p.opt.reg_bits, W));
-  s.passes = plan_passes(p, s.ops, s.reg_bits);
+  s.passes = plan_passes(p, p.opt, s.ops, s.reg_bits);
   int rc = build_late4(p, s, err);
   if (rc) return rc;
   absorb_one_qubit_gates(&s.late, s.s_bits);
@@ -1267,6 +1267,16 @@ Pass plan_one_tile(const Plan& p, const Schedule& s, int R) {
   ps.R = pass_reg_bits(R, p.h);
   plan_phases(ps, s.ops, ps.R, false);
   return ps;
+}
+
+std::vector<Pass> plan_tiles(const Plan& p, const Schedule& s, int T, int lo, int R) {
+  Options o = p.opt;
+  o.max_tile_bits = T;
+  o.low_bits = lo;
+  o.reg_bits = R;
+  o.math = 0;
+  o.reg_adapt = 0;
+  return plan_passes(p, o, s.ops, R);
 }
 
 int get_schedule(Plan& p, int k, std::shared_ptr<Schedule>* out, std::string* err) {
@@ -1307,7 +1317,7 @@ int get_schedule(Plan& p, int k, std::shared_ptr<Schedule>* out, std::string* er
     for (size_t i = start; i < ro.size(); ++i) s->ops.push_back(ro[i]);
   }
   s->reg_bits = std::max(1, std::min(p.opt.reg_bits, p.h));
-  s->passes = plan_passes(p, s->ops, s->reg_bits);
+  s->passes = plan_passes(p, p.opt, s->ops, s->reg_bits);
   // late program
   const int d = p.d;
   std::vector<double> cost;

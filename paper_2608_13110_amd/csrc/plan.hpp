@@ -156,6 +156,7 @@ struct Options {
   int bond = 0;             // entangler bond dimension of the lowering: 0 the smallest that holds
                             // every gate, 2, or 4
   uint64_t mem_cap_bytes = 0;  // device memory per call (0: no cap)
+  bool tiles_auto = false;  // no tile option was given: complex64 calls may run other tiles than these
 };
 
 // Everything that depends on k (the number of open output legs).
@@ -217,6 +218,11 @@ int get_schedule(Plan& p, int k, std::shared_ptr<Schedule>* out, std::string* er
 // The whole sweep as one pass over the single tile [0, p.h), 2^R entries per
 // thread, every update on its own (no fused phases).
 Pass plan_one_tile(const Plan& p, const Schedule& s, int R);
+
+// The sweep's passes over 2^T-entry tiles with `lo` low slots and 2^R entries
+// per thread, every update on its own: other passes than the plan's options
+// ask for, the same updates in the same order.
+std::vector<Pass> plan_tiles(const Plan& p, const Schedule& s, int T, int lo, int R);
 
 // FP64 host execution of the plan's own tables (planner self-check; the GPU
 // path never calls this).  out: n_batches * 2^k amplitudes.

@@ -70,11 +70,7 @@ int ring_layout(tnc_ring_plan_t ring, int32_t k, int32_t n_batches, uint64_t lau
 // for every slice), from the plan alone (no device involved).
 int slice_launches(tnc_ring_plan_t ring, int32_t k, int32_t n_batches, uint64_t* count) {
   (void)n_batches;
-  tnc_info info;
-  const int rc = tnc_plan_info(ring->slices[0], k, &info);
-  if (rc) return rc;
-  *count = 2 + (uint64_t)info.n_passes + (uint64_t)info.n_late_launches;
-  return TNC_OK;
+  return tnc::max_launches(ring->slices[0], k, count);
 }
 
 // out = L * X for 2x2 row-major complex matrices.

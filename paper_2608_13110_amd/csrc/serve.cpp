@@ -311,8 +311,9 @@ void ServerImpl::planner_loop() {
       rc = cp->rc;
     }
     tnc_info info{};
-    uint64_t ws = 0;
+    uint64_t ws = 0, launches = 0;
     if (!rc) rc = tnc_plan_info(cp->plan, r->k, &info);
+    if (!rc) rc = max_launches(cp->plan, r->k, &launches);
     if (!rc) rc = tnc_prepare(cp->plan, r->k);
     if (!rc) rc = tnc_workspace_bytes(cp->plan, r->k, r->nb, r->storage, &ws);
     const std::string perr = rc ? std::string("serving: planning: ") + tnc_last_error() : std::string();
@@ -322,7 +323,7 @@ void ServerImpl::planner_loop() {
     r->rc = rc;
     r->h = info.boundary_bits;
     r->ws_bytes = ws;
-    r->n_launches = 2 + info.n_passes + info.n_late_launches;
+    r->n_launches = (int)launches;
     r->footprint = req_layout(*r).total;
     r->small = opt.small_bits > 0 && r->h <= opt.small_bits;
     r->t_ready = now_ns();

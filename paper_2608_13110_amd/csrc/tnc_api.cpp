@@ -51,6 +51,13 @@ struct PassHost {
   int R = 5;
 };
 
+// A pass of the latency kernel.
+struct WinHost {
+  Window w;
+  int R = 2;
+  int phase_off = 0, n_phases = 0, slot_off = 0;
+};
+
 struct HostTables {
   std::vector<DevOp> ops;
   std::vector<float> mats;
@@ -62,8 +69,10 @@ struct HostTables {
   LatePlan late;
   std::vector<LateOpDev> prog;
   uint64_t bytes_late[2] = {0, 0};
-  // the one-launch kernel's tables (one: the schedule takes it)
+  // the one-launch kernel's tables (one: the schedule takes it), or those of the
+  // latency kernel's passes (wins)
   bool one = false;
+  std::vector<WinHost> wins;
   std::vector<OnePhase> one_phases;
   std::vector<OneSlot> one_slots;
   std::vector<double2> one_seg;
@@ -172,31 +181,24 @@ void fused_operand(const float* U32, float4* lanes) {
   }
 }
 
-// The tables of the one-launch kernel, where the call takes it: a tensor that
-// is one LDS tile of the kernel, updates on their own (fused products round
-// differently and stay on the pass kernel), and a join small enough for one
-// block (2^(h + k) FP64 products: 2^18 take it 7 us; above, the join's own
-// kernels spread them over the chip).
-void build_one(const Plan& p, const Schedule& s, HostTables* t) {
-  const int R = one_reg_bits(p.h), h = p.h;
-  if (p.chi != 2 || R == 0 || h + s.k > 18) return;
-  for (const Pass& ps : s.passes)
-    for (const Phase& ph : ps.phases)
-      if (ph.mf != 0) return;
-  const Pass ps = plan_one_tile(p, s, R);
-  if (ps.R != R) return;
+// A pass's phases and slots in the form of the one-launch and latency kernels;
+// false if it has others than those kernels run.
+bool one_tables(const Schedule& s, const Pass& ps, int R, std::vector<OnePhase>* phases, std::vector<OneSlot>* slots) {
+  const int T = ps.w.tile_bits();
+  if (ps.R != R) return false;
   for (const Phase& ph : ps.phases) {
     const int n_ops = ph.op_end - ph.op_begin;
-    if (ph.mf != 0 || n_ops < 1 || n_ops > R) return;
+    if (ph.mf != 0 || n_ops < 1 || n_ops > R) return false;
     OnePhase o;
     std::memset(&o, 0, sizeof(o));
     o.n_ops = n_ops;
+    auto local = [&](int slot) { return slot < 0 ? -1 : ps.w.contains(slot) ? ps.w.local(slot) : -2; };
     const SweepOp& first = s.ops[ph.op_begin];
-    const int ctl = first.kind == OP_CU ? first.control : -1;
-    bool ctl_found = ctl < 0;
+    const int ctl = first.kind == OP_CU ? local(first.control) : -1;
+    bool ctl_found = ctl == -1;
     uint32_t seen = 0;
     for (int b = 0; b < R; ++b) {
-      if (ph.reg[b] < 0 || ph.reg[b] >= h || (seen >> ph.reg[b] & 1u)) return;
+      if (ph.reg[b] < 0 || ph.reg[b] >= T || (seen >> ph.reg[b] & 1u)) return false;
       seen |= 1u << ph.reg[b];
     }
     for (int i = 0; i < (1 << R); ++i) {
@@ -205,8 +207,8 @@ void build_one(const Plan& p, const Schedule& s, HostTables* t) {
         if (i >> b & 1) r |= 1u << ph.reg[b];
       o.off[i] = swz(r) << 3;
     }
-    for (int q = 0; q < h - R; ++q) {
-      if (ph.tpos[q] < 0 || ph.tpos[q] >= h || (seen >> ph.tpos[q] & 1u)) return;
+    for (int q = 0; q < T - R; ++q) {
+      if (ph.tpos[q] < 0 || ph.tpos[q] >= T || (seen >> ph.tpos[q] & 1u)) return false;
       seen |= 1u << ph.tpos[q];
       const uint32_t w = (swz(1u << ph.tpos[q]) << 3) | (ph.tpos[q] == ctl ? kOneCtl : 0u);
       for (int i = 0; i < (q < 4 ? 16 : 32); ++i)
@@ -215,11 +217,11 @@ void build_one(const Plan& p, const Schedule& s, HostTables* t) {
     }
     for (int b = 0; b < n_ops; ++b) {
       const SweepOp& op = s.ops[ph.op_begin + b];
-      if ((op.kind != OP_CU && (b > 0 || op.kind != OP_DUP)) || op.target != ph.reg[b]) return;
-      if (b > 0 && op.control != ph.reg[b - 1]) return;
+      if ((op.kind != OP_CU && (b > 0 || op.kind != OP_DUP)) || local(op.target) != ph.reg[b]) return false;
+      if (b > 0 && (op.control < 0 || local(op.control) != ph.reg[b - 1])) return false;
     }
-    if (!ctl_found) return;
-    t->one_phases.push_back(o);
+    if (!ctl_found) return false;
+    phases->push_back(o);
     for (int b = 0; b < R; ++b) {
       OneSlot sl{-1, -1, -1};
       if (b < n_ops) {
@@ -227,8 +229,48 @@ void build_one(const Plan& p, const Schedule& s, HostTables* t) {
         sl.xrow0 = (int16_t)s.ops[sl.op].xrow[0];
         sl.xrow1 = (int16_t)s.ops[sl.op].xrow[1];
       }
-      t->one_slots.push_back(sl);
+      slots->push_back(sl);
     }
+  }
+  return true;
+}
+
+// The tables of the one-launch kernel, where the call takes it: a tensor that
+// is one LDS tile of the kernel, updates on their own (fused products round
+// differently and stay on the pass kernel), and a join small enough for one
+// block (2^(h + k) FP64 products: 2^18 take it 7 us; above, the join's own
+// kernels spread them over the chip).  And of the latency kernel: tensors of
+// 2^13 to 2^20 entries planned without tile options of the caller's.
+void build_one(const Plan& p, const Schedule& s, HostTables* t) {
+  const int h = p.h;
+  if (p.chi != 2) return;
+  for (const Pass& ps : s.passes)
+    for (const Phase& ph : ps.phases)
+      if (ph.mf != 0) return;
+  if (one_reg_bits(h) > 0 && h + s.k <= 18) {
+    t->one = one_tables(s, plan_one_tile(p, s, one_reg_bits(h)), one_reg_bits(h), &t->one_phases, &t->one_slots);
+  } else if (h > kOneMaxBits && h <= kWinMaxBits && p.opt.tiles_auto) {
+    const int T = win_tile_bits(h), R = win_reg_bits(T);
+    for (const Pass& ps : plan_tiles(p, s, T, win_low_bits(h), R)) {
+      WinHost w;
+      w.w = ps.w;
+      w.R = ps.R;
+      w.phase_off = (int)t->one_phases.size();
+      w.slot_off = (int)t->one_slots.size();
+      // the narrower top window may take fewer register bits or threads than the kernel has
+      if ((ps.R != 2 && ps.R != 3) || ps.w.tile_bits() - ps.R < (ps.R == 3 ? 8 : 6) ||
+          !one_tables(s, ps, ps.R, &t->one_phases, &t->one_slots)) {
+        t->wins.clear();
+        break;
+      }
+      w.n_phases = (int)t->one_phases.size() - w.phase_off;
+      t->wins.push_back(w);
+    }
+  }
+  if (!t->one && t->wins.empty()) {
+    t->one_phases.clear();
+    t->one_slots.clear();
+    return;
   }
   auto d2 = [](cd z) { return make_double2(z.real(), z.imag()); };
   for (int w = 0; w < 2; ++w) t->one_seg.push_back(d2(p.init_v[w]));
@@ -236,7 +278,6 @@ void build_one(const Plan& p, const Schedule& s, HostTables* t) {
     for (int w = 0; w < 2; ++w) t->one_seg.push_back(d2(p.init_f[x][w]));
   for (int q = 0; q < 4; ++q) t->one_seg.push_back(t->late.final_kind == L_DOT ? d2(t->late.dot[q]) : make_double2(0, 0));
   t->one_seg.insert(t->one_seg.end(), t->seg.begin(), t->seg.end());
-  t->one = true;
 }
 
 int build_tables(Plan& p, const Schedule& s, HostTables* t, std::string* err) {
@@ -640,7 +681,7 @@ int check_storage(const HostTables& t, int storage) {
 // Device copy of the tables for one (k, device).
 struct DevSched {
   int device = -1;
-  HostTables host;
+  std::shared_ptr<const HostTables> tables;  // (the plan's own)
   char* arena = nullptr;  // all of the following
   DevOp* d_ops = nullptr;
   float* d_mats = nullptr;
@@ -669,6 +710,10 @@ struct DevSched {
 };
 
 struct PlanDevice {
+  // the host tables per k, built once: sizes, launch counts and the device
+  // tables of a plan all come from them
+  std::mutex tables_mu;
+  std::map<int, std::shared_ptr<const HostTables>> tables;
   std::mutex mu;
   std::map<std::pair<int, int>, std::shared_ptr<DevSched>> m;
 };
@@ -682,6 +727,24 @@ PlanDevice& plan_device(Plan& p) {
     p.device_free = free_plan_device;
   }
   return *static_cast<PlanDevice*>(p.device);
+}
+
+int get_tables(Plan& p, int k, std::shared_ptr<const HostTables>* out) {
+  std::shared_ptr<Schedule> s;
+  std::string err;
+  int rc = get_schedule(p, k, &s, &err);
+  if (rc) return set_err(rc, err);
+  PlanDevice& pd = plan_device(p);
+  std::lock_guard<std::mutex> lk(pd.tables_mu);
+  std::shared_ptr<const HostTables>& t = pd.tables[k];
+  if (!t) {
+    auto made = std::make_shared<HostTables>();
+    rc = build_tables(p, *s, made.get(), &err);
+    if (rc) return set_err(rc, err);
+    t = made;
+  }
+  *out = t;
+  return 0;
 }
 
 template <typename T>
@@ -728,27 +791,24 @@ int get_dev_sched(Plan& p, int k, std::shared_ptr<DevSched>* out) {
     *out = it->second;
     return 0;
   }
-  std::shared_ptr<Schedule> s;
-  std::string err;
-  int rc = get_schedule(p, k, &s, &err);
-  if (rc) return set_err(rc, err);
   auto ds = std::make_shared<DevSched>();
   ds->device = dev;
-  rc = build_tables(p, *s, &ds->host, &err);
-  if (rc) return set_err(rc, err);
+  int rc = get_tables(p, k, &ds->tables);
+  if (rc) return rc;
+  const HostTables& host = *ds->tables;
   TableUpload up;
-  up.add(&ds->d_ops, ds->host.ops);
-  up.add(&ds->d_mats, ds->host.mats);
-  up.add(&ds->d_phases, ds->host.phases);
-  up.add(&ds->d_poffs, ds->host.poffs);
-  up.add(&ds->d_fmats, ds->host.fmats);
-  up.add(&ds->d_seg, ds->host.seg);
+  up.add(&ds->d_ops, host.ops);
+  up.add(&ds->d_mats, host.mats);
+  up.add(&ds->d_phases, host.phases);
+  up.add(&ds->d_poffs, host.poffs);
+  up.add(&ds->d_fmats, host.fmats);
+  up.add(&ds->d_seg, host.seg);
   static_assert(sizeof(cd) == sizeof(double2), "(re, im)");
-  up.add(reinterpret_cast<cd**>(&ds->d_J), ds->host.late.first.J);
-  up.add(&ds->d_prog, ds->host.prog);
-  up.add(&ds->d_one_phases, ds->host.one_phases);
-  up.add(&ds->d_one_slots, ds->host.one_slots);
-  up.add(&ds->d_one_seg, ds->host.one_seg);
+  up.add(reinterpret_cast<cd**>(&ds->d_J), host.late.first.J);
+  up.add(&ds->d_prog, host.prog);
+  up.add(&ds->d_one_phases, host.one_phases);
+  up.add(&ds->d_one_slots, host.one_slots);
+  up.add(&ds->d_one_seg, host.one_seg);
   if ((rc = up.run(&ds->arena))) return rc;
   pd.m[{k, dev}] = ds;
   *out = ds;
@@ -923,8 +983,39 @@ LateOpsArgs ops_args(const Plan& p, const HostTables& t, const LateOpsLaunch& ln
   return a;
 }
 
+// The latency kernel's passes are taken while the tensors of a call leave the
+// chip part empty: up to 2^20 entries together (2^19 at 2^13 entries each, where
+// the pass kernel holds a tensor in one tile).  us per call of 40 qubits, k = 0,
+// latency kernel and pass kernel: 2^15 entries, 32 batches 460 / 758, 64 batches
+// 793 / 846 (632 with smaller tiles); 2^17, 8 batches 521 / 755, 16 batches
+// 875 / 841; 2^20, 1 batch 618 / 962, 2 batches 1078 / 1239; 2^13, 64 batches
+// 321 / 436, 128 batches 459 / 441.
+bool use_wins(const Plan& p, int nb) { return ((uint64_t)nb << p.h) <= (p.h == 13 ? 1ull << 19 : 1ull << 20); }
+
+WinArgs win_args(const Plan& p, const DevSched& ds, const WinHost& w, bool init, float2* B, const uint8_t* bits, int nb) {
+  WinArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.phases = ds.d_one_phases + w.phase_off;
+  a.slots = ds.d_one_slots + w.slot_off;
+  a.mats = ds.d_mats;
+  a.seg = ds.d_one_seg;
+  a.bits = bits;
+  a.B = B;
+  a.n_phases = w.n_phases;
+  a.n = p.n;
+  a.h = p.h;
+  a.m0 = p.m0;
+  a.T = w.w.tile_bits();
+  a.lo_bits = w.w.lo_bits;
+  a.win_lo = w.w.win_lo;
+  a.win_len = w.w.win_len;
+  a.n_tiles = nb << (p.h - a.T);
+  a.init = init ? 1 : 0;
+  return a;
+}
+
 OneArgs one_args(const Plan& p, const DevSched& ds, int nb, const uint8_t* bits, int k, double2* out) {
-  const HostTables& t = ds.host;
+  const HostTables& t = *ds.tables;
   const LateFirst& F = t.late.first;
   OneArgs a;
   std::memset(&a, 0, sizeof(a));
@@ -963,7 +1054,7 @@ OneArgs one_args(const Plan& p, const DevSched& ds, int nb, const uint8_t* bits,
 // variant resolution, the passes, the join and the late launches.
 int record_launches(Plan& p, DevSched& ds, int nb_total, const uint8_t* d_bits, int k, int storage, tnc_c128* d_out,
                     void* ws, uint64_t ws_bytes, std::vector<Launch>* out) {
-  const HostTables& t = ds.host;
+  const HostTables& t = *ds.tables;
   int rc = check_storage(t, storage);
   if (rc) return rc;
   const bool s16 = is_s16(storage);
@@ -999,6 +1090,7 @@ int record_launches(Plan& p, DevSched& ds, int nb_total, const uint8_t* d_bits, 
     double2* L1 = reinterpret_cast<double2*>(q + L.late0 * nb);
     const uint8_t* bits = d_bits + (size_t)b0 * p.n;
     double2* outp = reinterpret_cast<double2*>(d_out) + ((size_t)b0 << k);
+    const bool win = !s16 && !t.wins.empty() && use_wins(p, nb);
     InitArgs ia = init_args(p, t, B, bits, nb, ds.d_seg);
     if (s16) {
       ia.store = storage;
@@ -1006,8 +1098,10 @@ int record_launches(Plan& p, DevSched& ds, int nb_total, const uint8_t* d_bits, 
       ia.scale_stride = sstride;
       ia.blk_bits = std::min(12, p.h);
     }
-    if (record_init(ia, &rec) != hipSuccess) return shape_err("row-0 build-up");
-    out->push_back(rec);
+    if (!win) {
+      if (record_init(ia, &rec) != hipSuccess) return shape_err("row-0 build-up");
+      out->push_back(rec);
+    }
     ResolveArgs ra;
     std::memset(&ra, 0, sizeof(ra));
     ra.ops = ds.d_ops;
@@ -1018,14 +1112,21 @@ int record_launches(Plan& p, DevSched& ds, int nb_total, const uint8_t* d_bits, 
     ra.n_ops = (int)t.ops.size();
     ra.n = p.n;
     ra.n_batches = nb;
-    if (ra.n_ops > 0) {
+    if (ra.n_ops > 0 && !win) {
       if (record_resolve(ra, &rec) != hipSuccess) return shape_err("variant resolution");
       out->push_back(rec);
     }
     const double pass_bytes = 2.0 * (s16 ? 4.0 : 8.0) * (double)(1ull << p.h) * nb;
     int cur = 0;
     ScaleMap map = init_map(p);
+    for (size_t i = 0; win && i < t.wins.size(); ++i) {
+      if (record_win(win_args(p, ds, t.wins[i], i == 0, B, bits, nb), t.wins[i].R, &rec) != hipSuccess)
+        return shape_err("pass");
+      rec.bytes = pass_bytes;
+      out->push_back(rec);
+    }
     for (const PassHost& ph : t.passes) {
+      if (win) break;
       PassArgs a = pass_args(p, ph, ds.d_phases, ds.d_poffs, ds.d_fmats, B, bits, nb);
       a.rmats = rmats;
       a.rstride = rstride;
@@ -1099,7 +1200,7 @@ uint64_t c128_per_batch(const Plan& p, const HostTables& t) {
 
 int run_c128(Plan& p, DevSched& ds, int nb_total, const uint8_t* d_bits, int k, tnc_c128* d_out, void* ws,
              uint64_t ws_bytes, hipStream_t stream) {
-  const HostTables& t = ds.host;
+  const HostTables& t = *ds.tables;
   std::shared_ptr<Schedule> s;
   std::string err;
   int rc = get_schedule(p, k, &s, &err);
@@ -1177,9 +1278,9 @@ int emulate(Plan& p, int k, int nb, const uint8_t* bits, int storage, cd* out) {
   std::string err;
   int rc = get_schedule(p, k, &s, &err);
   if (rc) return set_err(rc, err);
-  HostTables t;
-  rc = build_tables(p, *s, &t, &err);
-  if (rc) return set_err(rc, err);
+  std::shared_ptr<const HostTables> tables;
+  if ((rc = get_tables(p, k, &tables))) return rc;
+  const HostTables& t = *tables;
   if (p.h > 24) return set_err(TNC_E_DOMAIN, "emulation limited to width 24");
   if ((rc = check_storage(t, storage))) return rc;
   const bool s16 = is_s16(storage);
@@ -1363,6 +1464,20 @@ int record_amplitudes(tnc_plan_t plan, int32_t n_batches, const uint8_t* d_bits,
   return record_launches(*p, *ds, n_batches, d_bits, k, storage, d_out, d_workspace, workspace_bytes, out);
 }
 
+int max_launches(tnc_plan_t plan, int32_t k, uint64_t* count) {
+  Plan* p = get(plan);
+  if (!p || !count) return set_err(TNC_E_INVALID, "null argument");
+  std::shared_ptr<Schedule> s;
+  std::string err;
+  int rc = get_schedule(*p, k, &s, &err);
+  if (rc) return set_err(rc, err);
+  std::shared_ptr<const HostTables> tables;
+  if ((rc = get_tables(*p, k, &tables))) return rc;
+  const HostTables& t = *tables;
+  *count = 3 + (uint64_t)std::max(t.passes.size(), t.wins.size()) + (uint64_t)t.late.ops.size();
+  return TNC_OK;
+}
+
 int issue_recorded(const std::vector<Launch>& ls, hipStream_t stream) { return issue_all(ls, stream); }
 }  // namespace tnc
 
@@ -1385,6 +1500,7 @@ int tnc_plan(int32_t n, int32_t d, const tnc_c128* one_qubit, int32_t n_gate2, c
     o.bond = opt->bond;
     o.mem_cap_bytes = opt->mem_cap_bytes;
   }
+  o.tiles_auto = !opt || (!opt->max_tile_bits && !opt->reg_bits && !opt->low_bits && !opt->math && !opt->reg_adapt);
   if (o.max_tile_bits < 6 || o.max_tile_bits > 14 || o.reg_bits < 1 || o.reg_bits > 5 || o.low_bits < 1 ||
       o.low_bits > o.max_tile_bits - 2 || (o.math != 0 && o.math != 2) || o.late_fold < -1 || o.late_fold > 8 ||
       o.reg_adapt < 0 || o.reg_adapt > 1 || o.max_tile_bits - o.reg_bits > 9 ||
@@ -1417,9 +1533,9 @@ int tnc_plan_info(tnc_plan_t plan, int32_t k, tnc_info* info) {
   std::string err;
   int rc = get_schedule(*p, k, &s, &err);
   if (rc) return set_err(rc, err);
-  HostTables t;
-  rc = build_tables(*p, *s, &t, &err);
-  if (rc) return set_err(rc, err);
+  std::shared_ptr<const HostTables> tables;
+  if ((rc = get_tables(*p, k, &tables))) return rc;
+  const HostTables& t = *tables;
   std::memset(info, 0, sizeof(*info));
   info->width = s->width;
   info->boundary_bits = p->h;
@@ -1451,9 +1567,9 @@ int tnc_workspace_bytes(tnc_plan_t plan, int32_t k, int32_t n_batches, int32_t s
   std::string err;
   int rc = get_schedule(*p, k, &s, &err);
   if (rc) return set_err(rc, err);
-  HostTables t;
-  rc = build_tables(*p, *s, &t, &err);
-  if (rc) return set_err(rc, err);
+  std::shared_ptr<const HostTables> tables;
+  if ((rc = get_tables(*p, k, &tables))) return rc;
+  const HostTables& t = *tables;
   if ((rc = check_storage(t, storage))) return rc;
   if (p->h > kMaxDeviceWidth) return set_err(TNC_E_DOMAIN, "boundary tensors above 2^40 entries are planned only");
   const uint64_t per = batch_layout(*p, t, storage).per_batch();
@@ -1489,9 +1605,9 @@ int tnc_amplitudes_noalloc(tnc_plan_t plan, int32_t n_batches, const uint8_t* d_
   if (!ds)
     return set_err(TNC_E_INVALID, "device tables for these open legs are not prepared on this device "
                                   "(call tnc_prepare first; this entry point allocates nothing)");
-  int rc = check_storage(ds->host, storage);
+  int rc = check_storage(*ds->tables, storage);
   if (rc) return rc;
-  const uint64_t per = batch_layout(*p, ds->host, storage).per_batch();
+  const uint64_t per = batch_layout(*p, *ds->tables, storage).per_batch();
   if (per > kNoAllocScratchBytes)
     return set_err(TNC_E_NOMEM, "one batch needs " + std::to_string(per) + " bytes of workspace, above the " +
                                     std::to_string(kNoAllocScratchBytes) + "-byte scratch of tnc_amplitudes_noalloc");
@@ -1518,9 +1634,9 @@ int tnc_debug_workspace_c128(tnc_plan_t plan, int32_t k, int32_t n_batches, uint
   std::string err;
   int rc = get_schedule(*p, k, &s, &err);
   if (rc) return set_err(rc, err);
-  HostTables t;
-  rc = build_tables(*p, *s, &t, &err);
-  if (rc) return set_err(rc, err);
+  std::shared_ptr<const HostTables> tables;
+  if ((rc = get_tables(*p, k, &tables))) return rc;
+  const HostTables& t = *tables;
   *bytes = (uint64_t)n_batches * c128_per_batch(*p, t);
   return TNC_OK;
 }
@@ -1726,9 +1842,9 @@ int tnc_debug_lds_conflicts(tnc_plan_t plan, int32_t k, int64_t* stats) {
   std::string err;
   int rc = get_schedule(*p, k, &s, &err);
   if (rc) return set_err(rc, err);
-  HostTables t;
-  rc = build_tables(*p, *s, &t, &err);
-  if (rc) return set_err(rc, err);
+  std::shared_ptr<const HostTables> tables;
+  if ((rc = get_tables(*p, k, &tables))) return rc;
+  const HostTables& t = *tables;
   // lanes 0..63 of a wave (thread index = lane); slot of register entry 0
   // (the other entries differ by a constant XOR); a group of g lanes
   // conflicts when two of its lanes meet the same slot modulo g
