@@ -1980,10 +1980,11 @@ __device__ inline void xeb_result(double sum, double sum2, long long total, int 
 
 // Sums of ln p and (ln p)^2 over this block's share of the components, valid
 // in thread 0.
+template <int NT>
 __device__ inline double2 xeb_block_sums(const double2* amps, int k, const int32_t* sel, long long total) {
-  __shared__ double s1[kBlock], s2[kBlock];
+  __shared__ double s1[NT], s2[NT];
   double a1 = 0.0, a2 = 0.0;
-  for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < total; i += (long long)gridDim.x * kBlock) {
+  for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i < total; i += (long long)gridDim.x * NT) {
     const long long idx = sel ? ((i << k) + sel[i]) : i;
     const double2 z = amps[idx];
     const double lp = log(z.x * z.x + z.y * z.y);
@@ -1993,7 +1994,7 @@ __device__ inline double2 xeb_block_sums(const double2* amps, int k, const int32
   s1[threadIdx.x] = a1;
   s2[threadIdx.x] = a2;
   __syncthreads();
-  for (int off = kBlock / 2; off > 0; off >>= 1) {
+  for (int off = NT / 2; off > 0; off >>= 1) {
     if ((int)threadIdx.x < off) {
       s1[threadIdx.x] += s1[threadIdx.x + off];
       s2[threadIdx.x] += s2[threadIdx.x + off];
@@ -2003,9 +2004,11 @@ __device__ inline double2 xeb_block_sums(const double2* amps, int k, const int32
   return make_double2(s1[0], s2[0]);
 }
 
-__global__ __launch_bounds__(kBlock) void k_logxeb(const double2* amps, long long total, int k, const int32_t* sel,
+// One block: up to 1024 components by 256 threads, up to kXebSingle by 1024.
+template <int NT>
+__global__ __launch_bounds__(NT) void k_logxeb(const double2* amps, long long total, int k, const int32_t* sel,
                                                    int n_qubits, double* result) {
-  const double2 s = xeb_block_sums(amps, k, sel, total);
+  const double2 s = xeb_block_sums<NT>(amps, k, sel, total);
   if (threadIdx.x == 0) xeb_result(s.x, s.y, total, n_qubits, result);
 }
 
@@ -2017,7 +2020,7 @@ __global__ __launch_bounds__(kBlock) void k_logxeb(const double2* amps, long lon
 // same from run to run, and their 100 bits add no rounding of note.  One block
 // computes 2051 x 256 logarithms in 780 us (one CU), 128 blocks in 17 us.
 constexpr int kXebBlocks = 128;  // (their sums meet at five addresses: 512 blocks took 37 us)
-constexpr long long kXebSingle = 4096;  // up to here one block is as fast (8 us) and needs no clearing launch
+constexpr long long kXebSingle = 8192;  // up to here one block of 1024 is as fast and needs no clearing launch
 static_assert(kXebBlocks < (1 << 12), "arrival fields of 16 bits, low words of 40 bits");
 
 // ln p of a finite nonzero double lies in (-746, 710): |sum| < total 2^10 and
@@ -2042,7 +2045,7 @@ __global__ void k_logxeb_clear(unsigned long long* acc) {
 
 __global__ __launch_bounds__(kBlock) void k_logxeb_blocks(const double2* amps, long long total, int k,
                                                           const int32_t* sel, int n_qubits, double* result) {
-  const double2 s = xeb_block_sums(amps, k, sel, total);
+  const double2 s = xeb_block_sums<kBlock>(amps, k, sel, total);
   if (threadIdx.x != 0) return;
   // word 4: arrivals, and how many sums were -inf (a zero probability), +inf, NaN
   unsigned long long* acc = reinterpret_cast<unsigned long long*>(result);
@@ -2070,8 +2073,11 @@ __global__ __launch_bounds__(kBlock) void k_logxeb_blocks(const double2* amps, l
 hipError_t launch_logxeb(const double2* amps, int n_batches, int k, const int32_t* sel, int n_qubits,
                          double* result, hipStream_t s) {
   const long long total = sel ? (long long)n_batches : (long long)n_batches << k;
+  if (total <= 1024)
+    return launch_direct(reinterpret_cast<const void*>(&k_logxeb<256>), dim3(1), dim3(256), s, amps, total, k, sel,
+                         n_qubits, result);
   if (total <= kXebSingle)
-    return launch_direct(reinterpret_cast<const void*>(&k_logxeb), dim3(1), dim3(kBlock), s, amps, total, k, sel,
+    return launch_direct(reinterpret_cast<const void*>(&k_logxeb<1024>), dim3(1), dim3(1024), s, amps, total, k, sel,
                          n_qubits, result);
   const hipError_t e = launch_direct(reinterpret_cast<const void*>(&k_logxeb_clear), dim3(1), dim3(64), s,
                                      reinterpret_cast<unsigned long long*>(result));

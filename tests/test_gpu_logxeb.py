@@ -20,8 +20,8 @@ def amps_of(nb, k, seed):
     return (rng.standard_normal(shape) + 1j * rng.standard_normal(shape)) * 2.0 ** -30
 
 
-# 4096 components end the single block; 128 blocks of 1024 end the grid's growth
-@pytest.mark.parametrize("nb,k,select", [(1, 0, False), (4096, 0, False), (4097, 0, False), (513, 3, False),
+# 1024 components end the small block, 8192 the single one; 128 blocks of 1024 end the grid's growth
+@pytest.mark.parametrize("nb,k,select", [(1, 0, False), (1024, 0, False), (1025, 0, False), (2048, 2, False), (2049, 2, False), (513, 3, False),
                                          (2051, 8, False), (2051, 8, True), (5000, 2, True), (1024, 10, False)])
 def test_logxeb_sizes(nb, k, select):
     from paper_2608_13110_amd import logxeb
@@ -43,7 +43,7 @@ def test_logxeb_sizes(nb, k, select):
 
 
 @pytest.mark.parametrize("value,want", [(0.0, -math.inf), (math.inf, math.inf), (math.nan, math.nan)])
-@pytest.mark.parametrize("nb", [100, 9000])
+@pytest.mark.parametrize("nb", [100, 9000, 20000])
 def test_logxeb_special_values(nb, value, want):
     # one zero, infinite or undefined probability decides the estimate
     from paper_2608_13110_amd import logxeb
