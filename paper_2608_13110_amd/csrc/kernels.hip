@@ -1856,25 +1856,47 @@ hipError_t launch_fill_zero(double2* out, long long count, hipStream_t s) {
                        dim3(kBlock), s, out, count);
 }
 
-// out[i] += in[r * stride + i] for r = 0..rows-1 in order (FP64).
+// out[i] += sum over r < rows of in[r * stride + i] (FP64).  A block takes W
+// consecutive outputs (W = 16, or fewer for a few): thread (g, i) sums rows g, g
+// + 256 / W, ..., and the groups' sums meet in LDS, in a fixed order.  One
+// thread per output, all rows in turn, left 16 threads to read 1024 rows: 240
+// us, 6 us here.
 __global__ __launch_bounds__(kBlock) void k_accumulate_rows(double2* out, const double2* in, long long stride,
-                                                           int rows, long long count) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= count) return;
-  double2 acc = out[i];
-  for (int r = 0; r < rows; ++r) {
-    const double2 v = in[(long long)r * stride + i];
-    acc.x += v.x;
-    acc.y += v.y;
+                                                           int rows, long long count, int W) {
+  __shared__ double2 part[kBlock];
+  const int i = threadIdx.x % W, g = threadIdx.x / W, G = kBlock / W;
+  const long long o = (long long)blockIdx.x * W + i;
+  double2 acc = make_double2(0.0, 0.0);
+  if (o < count) {
+#pragma unroll 8
+    for (int r = g; r < rows; r += G) {
+      const double2 v = in[(long long)r * stride + o];
+      acc.x += v.x;
+      acc.y += v.y;
+    }
   }
-  out[i] = acc;
+  part[threadIdx.x] = acc;
+  __syncthreads();
+  for (int h = G / 2; h > 0; h >>= 1) {
+    if (g < h) {
+      part[threadIdx.x].x += part[threadIdx.x + h * W].x;
+      part[threadIdx.x].y += part[threadIdx.x + h * W].y;
+    }
+    __syncthreads();
+  }
+  if (g == 0 && o < count) {
+    out[o].x += part[i].x;
+    out[o].y += part[i].y;
+  }
 }
 
 hipError_t launch_accumulate_rows(double2* out, const double2* in, long long stride, int rows, long long count,
                                   hipStream_t s) {
   if (count <= 0 || rows <= 0) return hipSuccess;
-  return launch_direct(reinterpret_cast<const void*>(&k_accumulate_rows),
-                       dim3((unsigned)((count + kBlock - 1) / kBlock)), dim3(kBlock), s, out, in, stride, rows, count);
+  int W = 1;
+  while (W < 16 && W < count) W *= 2;
+  return launch_direct(reinterpret_cast<const void*>(&k_accumulate_rows), dim3((unsigned)((count + W - 1) / W)),
+                       dim3(kBlock), s, out, in, stride, rows, count, W);
 }
 
 

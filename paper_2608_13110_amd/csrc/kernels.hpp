@@ -702,7 +702,7 @@ hipError_t launch_op64(const Op64Args& a, hipStream_t s);
 
 // Launchers of the kernels outside the amplitude path (kernels.hip).
 hipError_t launch_fill_zero(double2* out, long long count, hipStream_t s);
-// out[i] += sum over r < rows of in[r * stride + i], added in row order.
+// out[i] += sum over r < rows of in[r * stride + i], in a fixed order.
 hipError_t launch_accumulate_rows(double2* out, const double2* in, long long stride, int rows, long long count,
                                   hipStream_t s);
 // Batched sampling handles up to 2^10 suffixes per batch: 4 per thread.

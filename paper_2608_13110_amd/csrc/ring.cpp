@@ -231,7 +231,7 @@ int tnc_ring_amplitudes(tnc_ring_plan_t ring, int32_t n_batches, const uint8_t* 
       if ((e = tnc::issue_grouped(steps[j].data(), G, base + seg_off[j], s)) != hipSuccess)
         return ring_err(TNC_E_DEVICE, hipGetErrorString(e));
     }
-    // the group's results added to the sum, slice by slice in index order
+    // the group's results added to the sum, in a fixed order
     e = tnc::launch_accumulate_rows(reinterpret_cast<double2*>(d_out), reinterpret_cast<const double2*>(out_base),
                                     L.per_out / sizeof(double2), G, count, s);
     if (e != hipSuccess) return ring_err(TNC_E_DEVICE, hipGetErrorString(e));
