@@ -65,6 +65,7 @@ struct HostTables {
   std::vector<uint32_t> poffs;  // kPhaseOffs per phase
   std::vector<float4> fmats;    // kFusedWords per phase (fused phases only; empty without them)
   std::vector<PassHost> passes;
+  std::vector<PassHost> sized;  // in their place for complex64 calls, where not empty
   std::vector<double2> seg;
   LatePlan late;
   std::vector<LateOpDev> prog;
@@ -179,6 +180,30 @@ void fused_operand(const float* U32, float4* lanes) {
     }
     lanes[l] = make_float4(v[0], v[1], v[2], v[3]);
   }
+}
+
+// Tiles of the pass kernel for a 2^h-entry tensor: as few windows as tiles of
+// 2^13 entries allow with at least four adjacent entries per run (eight from
+// 2^24 entries on, where the runs come from HBM), then the smallest tile with
+// that many windows (more blocks) and the longest runs.  16 entries per thread, 8
+// in the smaller tiles.  ms per call of 40 qubits, k = 0, one batch, for these
+// tiles and for one choice at every size (2^13 entries, 16-entry runs, 32 per
+// thread): 2^21 0.50 / 0.56, 2^23 2.24 / 3.32, 2^25 8.8 / 11.0, 2^26 19.5 / 22.1,
+// 2^28 80.3 / 85.0, 2^30 (30 qubits) 270 / 340; with 64 batches at 2^17 1.77 /
+// 2.03 and at 2^20 12.8 / 14.7.
+struct Tiles {
+  int T, lo, R;
+};
+Tiles tiles_for(int h) {
+  if (h <= 13) return {13, 4, 4};  // one window
+  if (h <= 18) return {std::max(10, (h + 5) / 2), 3, 3};
+  if (h <= 20) return {12, 3, 4};
+  if (h <= 23) return {13, std::min(3, 25 - h), 4};
+  if (h <= 26) return {12, 4, 4};  // three windows
+  if (h <= 29) return {13, 4, 4};
+  if (h <= 31) return {13, 3, 4};
+  if (h <= 34) return {13, 5, 4};  // four
+  return {13, 4, 4};
 }
 
 // A pass's phases and slots in the form of the one-launch and latency kernels;
@@ -374,7 +399,8 @@ int build_tables(Plan& p, const Schedule& s, HostTables* t, std::string* err) {
       for (int q = 0; q < 8; ++q)
         for (int e = 0; e < 8; ++e) t->mats[(o * 4 + q / 2) * 16 + (q & 1) * 8 + e] = e == 0 || e == 4 ? 1.f : 0.f;
   }
-  for (const Pass& ps : s.passes) {
+  // a pass's tables, appended
+  auto add_pass = [&](const Pass& ps, std::vector<PassHost>* out) -> int {
     PassHost ph;
     ph.w = ps.w;
     ph.R = ps.R;
@@ -596,7 +622,19 @@ int build_tables(Plan& p, const Schedule& s, HostTables* t, std::string* err) {
         t->ops[o] = d;
       }
     }
-    t->passes.push_back(ph);
+    out->push_back(ph);
+    return 0;
+  };
+  for (const Pass& ps : s.passes)
+    if (int rc = add_pass(ps, &t->passes)) return rc;
+  // complex64 calls of plans without tile options take tiles by the tensor's
+  // size; without fused products the passes only decide which updates share a
+  // pass, and every one is the same FP32 arithmetic (16-bit storage rounds at
+  // each pass and keeps the plan's own)
+  if (p.opt.tiles_auto && p.chi == 2 && p.h > kOneMaxBits) {
+    const Tiles c = tiles_for(p.h);
+    for (const Pass& ps : plan_tiles(p, s, c.T, c.lo, c.R))
+      if (int rc = add_pass(ps, &t->sized)) return rc;
   }
   t->seg.resize((size_t)std::max(0, p.m0 - 1) * 4);
   for (int j = 1; j < p.m0; ++j)
@@ -1125,7 +1163,7 @@ int record_launches(Plan& p, DevSched& ds, int nb_total, const uint8_t* d_bits, 
       rec.bytes = pass_bytes;
       out->push_back(rec);
     }
-    for (const PassHost& ph : t.passes) {
+    for (const PassHost& ph : !s16 && !t.sized.empty() ? t.sized : t.passes) {
       if (win) break;
       PassArgs a = pass_args(p, ph, ds.d_phases, ds.d_poffs, ds.d_fmats, B, bits, nb);
       a.rmats = rmats;
@@ -1474,7 +1512,7 @@ int max_launches(tnc_plan_t plan, int32_t k, uint64_t* count) {
   std::shared_ptr<const HostTables> tables;
   if ((rc = get_tables(*p, k, &tables))) return rc;
   const HostTables& t = *tables;
-  *count = 3 + (uint64_t)std::max(t.passes.size(), t.wins.size()) + (uint64_t)t.late.ops.size();
+  *count = 3 + (uint64_t)std::max({t.passes.size(), t.wins.size(), t.sized.size()}) + (uint64_t)t.late.ops.size();
   return TNC_OK;
 }
 

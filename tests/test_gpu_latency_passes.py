@@ -65,3 +65,22 @@ def test_same_updates_as_other_tiles(d):
     for got in (plan.amplitudes(bits, k), plan.amplitudes(bits[:-3].contiguous(), k), plan.amplitudes(bits, k, workspace=ws)):
         torch.cuda.synchronize()
         assert (got - ref[: len(got)]).abs().max().item() <= 1e-13 * ref.abs().max().item()
+
+
+@pytest.mark.parametrize("d,nb", [(25, 130), (26, 130), (28, 70), (31, 40), (34, 10), (36, 5), (37, 3), (40, 2), (41, 1),
+                                  (43, 1), (46, 1), (47, 1), (50, 1), (52, 1), (53, 1), (55, 1)])
+def test_tiles_by_size(d, nb):
+    # the tiles that calls without tile options take, at each change of the
+    # rule, against the plan's own tiles asked for by name: the same bits up to
+    # the FP64 late phase
+    from paper_2608_13110_amd import Plan
+    n, k = 7, 1
+    c = H.mixed_circuit(n, d, 23 * d, dense=0.3)
+    bits = torch.from_numpy(W.random_bitstrings(n, nb, W.rng_for(461, d))).cuda()
+    print(f"  [gpu] n={n} d={d} k={k} batches={nb}", flush=True)
+    got = Plan.from_circuit(c).amplitudes(bits, k)
+    ref = Plan.from_circuit(c, dict(max_tile_bits=13, low_bits=4, reg_bits=5)).amplitudes(bits, k)
+    torch.cuda.synchronize()
+    assert (got - ref).abs().max().item() <= 1e-13 * ref.abs().max().item()
+    per, _ = H.amp_errors(got.cpu().numpy(), oracle.amplitudes(c, bits.cpu().numpy(), k), n)
+    assert per < H.TOL_C64, per
