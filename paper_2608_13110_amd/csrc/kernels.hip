@@ -10,6 +10,7 @@
 //             the rest of the late program
 //  k_one      all of it in one launch for tensors of up to 2^12 entries
 //  k_win      the pass over tensors too small to fill the chip
+//  k_fold     the join matrix with late removals folded in, once per plan
 //  k_logxeb   FP64 log-XEB reduction; samplers
 //
 // The kernels of the amplitude path are recorded as launches (Launch, see
@@ -1326,6 +1327,67 @@ hipError_t record_late_ops(const LateOpsArgs& a, Launch* L) {
   L->gfn = reinterpret_cast<const void*>(&k_late_ops_g);
   set_arg(L, a);
   return set_shape(L, a.rows_out, (unsigned)a.n_batches, (unsigned)threads, lds);
+}
+
+// ---------------------------------------------------------------------------
+// The join matrix with j late removals folded in, once per plan and k: one row
+// per block, its 2^k-entry state in LDS.  On the host the fold of three removals
+// takes 21 ms at k = 8 and five about 100 ms; here 0.03 ms, so that calls of 2^23
+// entries have one too.
+__global__ __launch_bounds__(kBlock) void k_fold(const double2* Z, const LateOpDev* src_prog, int n_prog, int k, int j,
+                                                 double2* J) {
+  extern __shared__ __attribute__((aligned(16))) double2 st[];
+  const int dim = 1 << k;
+  LateOpDev* prog = reinterpret_cast<LateOpDev*>(st + dim);
+  const uint32_t row = blockIdx.x, u = row >> k;
+  const double2* in = Z + (size_t)(row & (uint32_t)(dim - 1)) * dim;
+  for (int i = threadIdx.x; i < dim; i += blockDim.x) st[i] = in[i];
+  int l = 0;
+  for (int o = 0; o < n_prog; ++o) {
+    if (o % kLateStage == 0) {
+      late_stage(prog, src_prog + o, n_prog - o);
+      __syncthreads();
+    }
+    const LateOpDev& op = prog[o % kLateStage];
+    const int kind = __builtin_amdgcn_readfirstlane(op.kind);
+    if (kind == 2) {
+      for (int w = threadIdx.x; w < dim / 4; w += blockDim.x) {
+        const int base = insert_zero(insert_zero(w, op.a), op.a + 1);
+        const int idx[4] = {base, base | (1 << (op.a + 1)), base | (1 << op.a), base | (3 << op.a)};
+        double2 x[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[q] = st[idx[q]];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const double2 p0 = zfma2(op.m[4 * q + 0], x[0], op.m[4 * q + 1], x[1]);
+          const double2 p1 = zfma2(op.m[4 * q + 2], x[2], op.m[4 * q + 3], x[3]);
+          st[idx[q]] = make_double2(p0.x + p1.x, p0.y + p1.y);
+        }
+      }
+    } else {  // a one-qubit gate, or a removal's matrix on bit 0
+      const int bit = kind == 3 ? 0 : op.a;
+      const double2* m = op.m + (kind == 3 ? 4 * ((u >> l) & 1u) : 0u);
+      for (int w = threadIdx.x; w < dim / 2; w += blockDim.x) {
+        const int i0 = insert_zero(w, bit), i1 = i0 | (1 << bit);
+        const double2 x0 = st[i0], x1 = st[i1];
+        st[i0] = zfma2(m[0], x0, m[1], x1);
+        st[i1] = zfma2(m[2], x0, m[3], x1);
+      }
+      if (kind == 3) ++l;
+    }
+    __syncthreads();  // (also ahead of the next ops' staging)
+  }
+  if (n_prog == 0) __syncthreads();
+  double2* out = J + (size_t)row * dim;
+  for (int i = threadIdx.x; i < dim; i += blockDim.x) out[i] = st[i];
+}
+
+hipError_t launch_fold(const double2* Z, const LateOpDev* prog, int n_prog, int k, int j, double2* J, hipStream_t s) {
+  if (!Z || !prog || !J || k < 1 || k > 10 || j < 0 || j > 12 || n_prog < 0) return hipErrorInvalidValue;
+  const int threads = std::max(64, std::min(kBlock, 1 << std::max(0, k - 2)));
+  const size_t lds = (sizeof(double2) << k) + sizeof(LateOpDev) * (size_t)std::min(kLateStage, n_prog);
+  void* args[] = {&Z, &prog, &n_prog, &k, &j, &J};
+  return hipLaunchKernel(reinterpret_cast<const void*>(&k_fold), dim3(1u << (k + j)), dim3((unsigned)threads), args, lds, s);
 }
 
 // ---------------------------------------------------------------------------

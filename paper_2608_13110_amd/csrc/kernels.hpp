@@ -700,6 +700,10 @@ hipError_t issue_grouped(const Launch* const* members, int n, const void* d_segs
 hipError_t launch_init64(const InitArgs& a, hipStream_t s);
 hipError_t launch_op64(const Op64Args& a, hipStream_t s);
 
+// J[(u << k) | e][t] = row e of Z (2^k x 2^k) taken through prog[0..n_prog), the
+// l-th removal with the matrix of bit l of u (u < 2^j).
+hipError_t launch_fold(const double2* Z, const LateOpDev* prog, int n_prog, int k, int j, double2* J, hipStream_t s);
+
 // Launchers of the kernels outside the amplitude path (kernels.hip).
 hipError_t launch_fill_zero(double2* out, long long count, hipStream_t s);
 // out[i] += sum over r < rows of in[r * stride + i], in a fixed order.

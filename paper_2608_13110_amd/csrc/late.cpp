@@ -57,7 +57,7 @@ int bitrev(int b, int k) {
 
 }  // namespace
 
-int build_late(const Plan& p, const Schedule& s, LatePlan* out, std::string* err) {
+int build_late(const Plan& p, const Schedule& s, LatePlan* out, std::string* err, int fold, bool host_join) {
   const auto& L = s.late;
   if (L.empty()) {
     if (err) *err = "empty late program";
@@ -95,7 +95,8 @@ int build_late(const Plan& p, const Schedule& s, LatePlan* out, std::string* err
     // 2^35-entry tensors (256 GiB of complex64) leave room for a join output
     // of 2^(h-j) x 16 B only with j = 7 (4 GiB).  From 2^30 entries on, j = 5
     // shrinks the late launches' input 32-fold; the join's flops do not depend on j.
-    const int want = p.opt.late_fold == 0 ? (s.m_fix >= 35 ? 7 : s.m_fix >= 30 ? 5 : s.m_fix >= 26 ? 3 : 0)
+    const int want = fold != -2 ? std::max(0, fold)
+                     : p.opt.late_fold == 0 ? (s.m_fix >= 35 ? 7 : s.m_fix >= 30 ? 5 : s.m_fix >= 26 ? 3 : 0)
                                           : std::max(0, p.opt.late_fold);
     j1 = std::min(nrem, std::min(want, k <= 8 ? 8 : 1));
   }
@@ -108,8 +109,10 @@ int build_late(const Plan& p, const Schedule& s, LatePlan* out, std::string* err
   const int js = slots_to[j1];
   const int ub = s.join_u_bits;
   const size_t de = size_t(1) << ub;
-  std::vector<cd> Ju(s.join.begin(), s.join.begin() + de * dim);
-  for (int i = 0; i < first_end; ++i) {
+  const bool on_device = !host_join && k >= 1 && js > 0 && !first_final;
+  std::vector<cd> Ju;
+  if (!on_device) Ju.assign(s.join.begin(), s.join.begin() + de * dim);
+  for (int i = 0; i < first_end && !on_device; ++i) {
     const LateOp& o = L[i];
     const size_t rows = Ju.size() >> sb;
     if (o.kind == L_U1) apply_u1(Ju.data(), rows, sb, o.a, o.m.data());
@@ -127,6 +130,7 @@ int build_late(const Plan& p, const Schedule& s, LatePlan* out, std::string* err
   LateFirst& F = out->first;
   F.j = js;
   F.final = first_final;
+  F.fold_ops = first_end;
   F.K = 1 << (ub + js);
   F.M = 1LL << (s.m_fix - ub - js);
   if (!first_final) {

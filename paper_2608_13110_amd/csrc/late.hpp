@@ -26,7 +26,8 @@ struct LateFirst {
   int nvar = 1;
   int j = 0;         // removals folded
   bool final = false;
-  std::vector<cd> J;  // [nvar][K][N]
+  std::vector<cd> J;  // [nvar][K][N]; empty: computed on the device (fold_ops)
+  int fold_ops = 0;   // late ops taken into J (Schedule::late [0, fold_ops))
 };
 
 struct LateOpsLaunch {
@@ -45,6 +46,9 @@ struct LatePlan {
   std::vector<cd> dot;   // L_DOT: f_0, f_1
 };
 
-int build_late(const Plan& p, const Schedule& s, LatePlan* out, std::string* err);
+// fold: removals folded into the join (-2: the plan's option).  host_join: J is
+// computed here; else, with removals folded and open legs, it is left to the
+// device.
+int build_late(const Plan& p, const Schedule& s, LatePlan* out, std::string* err, int fold = -2, bool host_join = true);
 
 }  // namespace tnc

@@ -51,6 +51,13 @@ struct PassHost {
   int R = 5;
 };
 
+// Removals folded into the join of a call of 2^23 entries or more: 2^8 blocks of
+// the join are left.  The join's flops do not depend on it, its output and the
+// late launches' input shrink eightfold (w = 20, k = 6, 64 batches: join and late
+// launches 1.98 ms without, 0.89 with; w = 24, k = 8: 0.98 and 0.76).
+constexpr int kFoldRemovals = 3;
+bool use_fold(int h, int nb) { return ((uint64_t)nb << h) >= (1ull << 23); }
+
 // A pass of the latency kernel.
 struct WinHost {
   Window w;
@@ -68,6 +75,11 @@ struct HostTables {
   std::vector<PassHost> sized;  // in their place for complex64 calls, where not empty
   std::vector<double2> seg;
   LatePlan late;
+  // the late phase with removals folded into the join, for calls whose join
+  // then still fills the chip (fold: there is one); its J is made on the device
+  bool fold = false;
+  LatePlan late_folded;
+  std::vector<cd> join;  // Z_early, where late.first.J is left to the device
   std::vector<LateOpDev> prog;
   uint64_t bytes_late[2] = {0, 0};
   // the one-launch kernel's tables (one: the schedule takes it), or those of the
@@ -640,8 +652,15 @@ int build_tables(Plan& p, const Schedule& s, HostTables* t, std::string* err) {
   for (int j = 1; j < p.m0; ++j)
     for (int e = 0; e < 4; ++e)
       t->seg[(size_t)(j - 1) * 4 + e] = make_double2(p.init_seg[j - 1].a[e].real(), p.init_seg[j - 1].a[e].imag());
-  int rc = build_late(p, s, &t->late, err);
+  // (the host emulation, which needs J, covers tensors up to 2^24)
+  int rc = build_late(p, s, &t->late, err, -2, p.h <= 24);
   if (rc) return rc;
+  if (t->late.first.J.empty()) t->join = s.join;
+  if (p.opt.late_fold == 0 && s.k >= 1 && s.k <= 8 && p.h > kOneMaxBits && t->late.first.j == 0 && !t->late.first.final &&
+      t->late.first.N == 1 << s.k && s.n_remove > kFoldRemovals) {
+    if ((rc = build_late(p, s, &t->late_folded, err, kFoldRemovals, false))) return rc;
+    t->fold = t->late_folded.first.J.empty();
+  }
   for (const LateOp& lo : s.late) {
     LateOpDev d;
     std::memset(&d, 0, sizeof(d));
@@ -660,6 +679,14 @@ int build_tables(Plan& p, const Schedule& s, HostTables* t, std::string* err) {
     const uint64_t bytes = align256((uint64_t)(ln.rows_in >> ln.j) * (16ull << t->late.s));
     uint64_t& slot = t->bytes_late[(i + 1) & 1];
     slot = std::max(slot, bytes);
+  }
+  // the folded late phase runs in the same buffers (every row count is smaller)
+  if (t->fold) {
+    const LatePlan& f = t->late_folded;
+    t->fold = align256((uint64_t)f.first.M * f.first.N * 16) <= t->bytes_late[0];
+    for (size_t i = 0; i < f.ops.size(); ++i)
+      if (!f.ops[i].final && align256((uint64_t)(f.ops[i].rows_in >> f.ops[i].j) * (16ull << f.s)) > t->bytes_late[(i + 1) & 1])
+        t->fold = false;
   }
   build_one(p, s, t);
   return 0;
@@ -728,6 +755,8 @@ struct DevSched {
   float4* d_fmats = nullptr;
   double2* d_seg = nullptr;
   double2* d_J = nullptr;
+  double2* d_Z = nullptr;         // Z_early, where J is made from it on the device
+  double2* d_folded[2] = {};      // J made on the device: of late, of late_folded (allocations of their own)
   LateOpDev* d_prog = nullptr;
   OnePhase* d_one_phases = nullptr;
   OneSlot* d_one_slots = nullptr;
@@ -739,7 +768,7 @@ struct DevSched {
     int prev = 0;
     if (device >= 0 && hipGetDevice(&prev) == hipSuccess) {
       (void)hipSetDevice(device);
-      void* ptrs[] = {arena, d_ops64};
+      void* ptrs[] = {arena, d_folded[0], d_folded[1], d_ops64};
       for (void* q : ptrs)
         if (q) (void)hipFree(q);
       (void)hipSetDevice(prev);
@@ -847,7 +876,23 @@ int get_dev_sched(Plan& p, int k, std::shared_ptr<DevSched>* out) {
   up.add(&ds->d_one_phases, host.one_phases);
   up.add(&ds->d_one_slots, host.one_slots);
   up.add(&ds->d_one_seg, host.one_seg);
+  if (!host.join.empty()) up.add(reinterpret_cast<cd**>(&ds->d_Z), host.join);
   if ((rc = up.run(&ds->arena))) return rc;
+  auto fold = [&](const LateFirst& F, const double2* Z, double2** J) -> int {
+    hipError_t e = hipMalloc((void**)J, (size_t)F.K * F.N * sizeof(double2));
+    if (e != hipSuccess) return set_err(TNC_E_NOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
+    e = launch_fold(Z, ds->d_prog, F.fold_ops, k, F.j, *J, nullptr);
+    return e == hipSuccess ? 0 : hip_err(e, "fold launch");
+  };
+  if (ds->d_Z) {
+    if ((rc = fold(host.late.first, ds->d_Z, &ds->d_folded[0]))) return rc;
+    ds->d_J = ds->d_folded[0];
+  }
+  if (host.fold && (rc = fold(host.late_folded.first, ds->d_J, &ds->d_folded[1]))) return rc;
+  if (ds->d_folded[0] || ds->d_folded[1]) {
+    const hipError_t e = hipStreamSynchronize(nullptr);  // other streams may read them next
+    if (e != hipSuccess) return hip_err(e, "fold");
+  }
   pd.m[{k, dev}] = ds;
   *out = ds;
   return 0;
@@ -975,9 +1020,9 @@ PassArgs pass_args(const Plan& p, const PassHost& ph, const DevPhase* phases, co
   return a;
 }
 
-LateArgs first_args(const Plan& p, const HostTables& t, const void* in, double2* out, long long out_stride,
+LateArgs first_args(const Plan& p, const LatePlan& late, const void* in, double2* out, long long out_stride,
                     const double2* J, const uint8_t* bits, int nb) {
-  const LateFirst& F = t.late.first;
+  const LateFirst& F = late.first;
   LateArgs a;
   std::memset(&a, 0, sizeof(a));
   a.in = in;
@@ -995,7 +1040,7 @@ LateArgs first_args(const Plan& p, const HostTables& t, const void* in, double2*
   return a;
 }
 
-LateOpsArgs ops_args(const Plan& p, const HostTables& t, const LateOpsLaunch& ln, const double2* in, double2* out,
+LateOpsArgs ops_args(const Plan& p, const LatePlan& late, const LateOpsLaunch& ln, const double2* in, double2* out,
                      long long out_stride, const LateOpDev* prog, const uint8_t* bits, int nb, int k) {
   LateOpsArgs a;
   std::memset(&a, 0, sizeof(a));
@@ -1004,20 +1049,20 @@ LateOpsArgs ops_args(const Plan& p, const HostTables& t, const LateOpsLaunch& ln
   a.bits = bits;
   a.prog = prog + ln.op_begin;
   a.n_prog = ln.op_end - ln.op_begin;
-  a.s = t.late.s;
+  a.s = late.s;
   a.j = ln.j;
-  a.in_batch_stride = ln.rows_in << t.late.s;
+  a.in_batch_stride = ln.rows_in << late.s;
   a.out_batch_stride = out_stride;
   a.rows_out = ln.rows_in >> ln.j;
   a.n_batches = nb;
   a.n = p.n;
   a.k = k;
-  a.final_kind = ln.final ? t.late.final_kind : 0;
-  a.final_xrow = t.late.final_xrow;
-  if (t.late.final_kind == L_DOT)
+  a.final_kind = ln.final ? late.final_kind : 0;
+  a.final_xrow = late.final_xrow;
+  if (late.final_kind == L_DOT)
     for (int x = 0; x < 2; ++x)
       for (int w = 0; w < 2; ++w)
-        a.dot[x][w] = make_double2(t.late.dot[2 * x + w].real(), t.late.dot[2 * x + w].imag());
+        a.dot[x][w] = make_double2(late.dot[2 * x + w].real(), late.dot[2 * x + w].imag());
   return a;
 }
 
@@ -1183,10 +1228,12 @@ int record_launches(Plan& p, DevSched& ds, int nb_total, const uint8_t* d_bits, 
         map = pass_map(ph);
       }
     }
-    const LateFirst& F = t.late.first;
+    const bool folded = t.fold && use_fold(p.h, nb_total);  // (by the whole call: groups do not change results)
+    const LatePlan& late = folded ? t.late_folded : t.late;
+    const LateFirst& F = late.first;
     double2* fout = F.final ? outp : L0;
     const long long fstride = F.final ? (1ll << k) : (long long)(t.bytes_late[0] / 16);
-    LateArgs fa = first_args(p, t, B, fout, fstride, ds.d_J, bits, nb);
+    LateArgs fa = first_args(p, late, B, fout, fstride, folded ? ds.d_folded[1] : ds.d_J, bits, nb);
     if (s16) {
       fa.store = storage;
       fa.scale_in = sc[cur];
@@ -1197,11 +1244,11 @@ int record_launches(Plan& p, DevSched& ds, int nb_total, const uint8_t* d_bits, 
     out->push_back(rec);
     const double2* curl = L0;
     long long cur_stride = fstride;
-    for (size_t i = 0; i < t.late.ops.size(); ++i) {
-      const LateOpsLaunch& ln = t.late.ops[i];
+    for (size_t i = 0; i < late.ops.size(); ++i) {
+      const LateOpsLaunch& ln = late.ops[i];
       double2* dst = ln.final ? outp : ((i + 1) & 1 ? L1 : L0);
       const long long dstride = ln.final ? (1ll << k) : (long long)(t.bytes_late[(i + 1) & 1] / 16);
-      LateOpsArgs a = ops_args(p, t, ln, curl, dst, dstride, ds.d_prog, bits, nb, k);
+      LateOpsArgs a = ops_args(p, late, ln, curl, dst, dstride, ds.d_prog, bits, nb, k);
       a.in_batch_stride = cur_stride;
       if (record_late_ops(a, &rec) != hipSuccess) return shape_err("late program");
       out->push_back(rec);
@@ -1288,7 +1335,7 @@ int run_c128(Plan& p, DevSched& ds, int nb_total, const uint8_t* d_bits, int k, 
     const LateFirst& F = t.late.first;
     double2* fout = F.final ? outp : L0;
     const long long fstride = F.final ? (1ll << k) : (long long)(t.bytes_late[0] / 16);
-    LateArgs fa = first_args(p, t, B, fout, fstride, ds.d_J, bits, nb);
+    LateArgs fa = first_args(p, t.late, B, fout, fstride, ds.d_J, bits, nb);
     std::vector<Launch> ls(1);
     if (record_late(fa, false, &ls[0]) != hipSuccess) return set_err(TNC_E_INVALID, "launch shape out of range: join");
     const double2* curl = L0;
@@ -1297,7 +1344,7 @@ int run_c128(Plan& p, DevSched& ds, int nb_total, const uint8_t* d_bits, int k, 
       const LateOpsLaunch& ln = t.late.ops[i];
       double2* dst = ln.final ? outp : ((i + 1) & 1 ? L1 : L0);
       const long long dstride = ln.final ? (1ll << k) : (long long)(t.bytes_late[(i + 1) & 1] / 16);
-      LateOpsArgs a = ops_args(p, t, ln, curl, dst, dstride, ds.d_prog, bits, nb, k);
+      LateOpsArgs a = ops_args(p, t.late, ln, curl, dst, dstride, ds.d_prog, bits, nb, k);
       a.in_batch_stride = cur_stride;
       Launch L;
       if (record_late_ops(a, &L) != hipSuccess) return set_err(TNC_E_INVALID, "launch shape out of range: late");

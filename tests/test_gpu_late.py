@@ -59,3 +59,24 @@ def test_first_late_launch(n, d, k, fold, nb, storage):
     torch.cuda.synchronize()
     per, l2 = H.amp_errors(got.cpu().numpy(), oracle.amplitudes(c, bits, k), n)
     assert per < (H.TOL_C64 if storage == "c64" else 4e-2), (per, l2)
+
+
+@pytest.mark.parametrize("d,k,nb", [(34, 3, 130), (40, 6, 9), (44, 8, 3), (46, 1, 1), (48, 5, 1), (50, 4, 1), (52, 2, 1)])
+def test_folded_join(d, k, nb):
+    # calls of 2^23 entries or more fold three removals into the join matrix on
+    # the device, from 2^26 entries on (and 2^25 with the option) so does the
+    # plan's own join: against the late phase without a fold (FP64 both: 1e-12)
+    # and the oracle
+    from paper_2608_13110_amd import Plan
+    n = 9
+    c = H.mixed_circuit(n, d, 29 * d + k, dense=0.3)
+    bits = W.random_bitstrings(n, nb, W.rng_for(463, d, k))
+    dev = torch.from_numpy(bits).cuda()
+    print(f"  [gpu] n={n} d={d} k={k} batches={nb}", flush=True)
+    ref = Plan.from_circuit(c, dict(late_fold=-1)).amplitudes(dev, k)
+    for options in (None, dict(late_fold=2)):
+        got = Plan.from_circuit(c, options).amplitudes(dev, k)
+        torch.cuda.synchronize()
+        assert (got - ref).abs().max().item() <= 1e-12 * ref.abs().max().item(), options
+    per, _ = H.amp_errors(ref.cpu().numpy(), oracle.amplitudes(c, bits, k), n)
+    assert per < H.TOL_C64, per
