@@ -226,6 +226,29 @@ __device__ __attribute__((always_inline)) inline unsigned xcd_block(uint32_t bx,
   return (gx & 7u) == 0u ? (bx & 7u) * (gx >> 3) + (bx >> 3) : bx;
 }
 
+// Tensors far larger than the 256 MiB last-level cache are read and written once
+// per pass, so their lines are marked as not to be kept (Stream, record_pass): a
+// call at w = 28 (2 GiB, k = 8) 139.0 -> 134.5 ms (writes alone 137.3), at w = 30
+// (k = 0, 30 qubits) 323 -> 303 ms.  At 1 GiB the marks change nothing (w = 27:
+// 39.8 ms both ways), at 256 MiB, where the cache serves the next pass, they cost
+// 7 % (bond four, w = 25: 5.39 -> 5.75 ms).  Runs below 128 bytes need the cache to
+// join them (128 batches at w = 20, 64-byte runs: 24.7 -> 26.7 ms).
+typedef float tnc_f4 __attribute__((ext_vector_type(4)));
+typedef uint32_t tnc_u4 __attribute__((ext_vector_type(4)));
+template <bool Stream>
+__device__ __attribute__((always_inline)) inline float4 hbm_get(const float2* p) {
+  if constexpr (Stream) {
+    const tnc_f4 v = __builtin_nontemporal_load(reinterpret_cast<const tnc_f4*>(p));
+    return make_float4(v.x, v.y, v.z, v.w);
+  }
+  return *reinterpret_cast<const float4*>(p);
+}
+template <bool Stream>
+__device__ __attribute__((always_inline)) inline void hbm_put(float2* p, float4 v) {
+  if constexpr (Stream) __builtin_nontemporal_store(tnc_f4{v.x, v.y, v.z, v.w}, reinterpret_cast<tnc_f4*>(p));
+  else *reinterpret_cast<float4*>(p) = v;
+}
+
 // LDS slots of the iteration parts it << shift (it < 32) of the entries a
 // thread stages: swz is linear, so the slot of it << shift is the XOR of the
 // slots of its set bits, taken from five values computed once per thread.
@@ -245,7 +268,7 @@ struct IterSlots {
   }
 };
 
-template <int R, bool MULTI, bool WU, int NT, int KIND>
+template <int R, bool MULTI, bool WU, int NT, int KIND, bool Stream>
 __device__ __attribute__((always_inline)) inline void pass_body(const PassArgs& a, float2* lds, uint32_t bx,
                                                                 uint32_t gx) {
   constexpr int E = 1 << R;
@@ -276,7 +299,7 @@ __device__ __attribute__((always_inline)) inline void pass_body(const PassArgs& 
 #pragma unroll
     for (int it = 0; it < E / 2; ++it) {
       const uint32_t i = (uint32_t)(it * tpt + (int)tt) * 2u;
-      ld[it] = *reinterpret_cast<const float4*>(Bt + tile_offset(i, a.lo_bits, a.win_lo));
+      ld[it] = hbm_get<Stream>(Bt + tile_offset(i, a.lo_bits, a.win_lo));
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -308,18 +331,18 @@ __device__ __attribute__((always_inline)) inline void pass_body(const PassArgs& 
       const uint32_t i = (uint32_t)(it * tpt + (int)tt) * 2u;
       const uint32_t si = isl.of(it) ^ st;
       const float4 val = *reinterpret_cast<const float4*>(region + pair_slot(si));
-      *reinterpret_cast<float4*>(Bt + tile_offset(i, a.lo_bits, a.win_lo)) = pair_order(val, pair_swapped(si));
+      hbm_put<Stream>(Bt + tile_offset(i, a.lo_bits, a.win_lo), pair_order(val, pair_swapped(si)));
     }
   }
 }
 
 // KIND 0: the bond-two phase forms (staircases, DUP, fused); KIND 1: the
 // bond-four ones (dense phases and single uncontrolled updates).
-template <int R, bool MULTI, bool WU, int NT = kBlock, int KIND = 0>
+template <int R, bool MULTI, bool WU, int NT = kBlock, int KIND = 0, bool Stream = false>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(pass_waves_per_eu<R, WU, NT>()))) void k_pass(
     PassArgs a) {
   extern __shared__ float2 lds[];
-  pass_body<R, MULTI, WU, NT, KIND>(a, lds, blockIdx.x, gridDim.x);
+  pass_body<R, MULTI, WU, NT, KIND, Stream>(a, lds, blockIdx.x, gridDim.x);
 }
 
 template <int R, bool MULTI, bool WU, int NT = kBlock, int KIND = 0>
@@ -329,7 +352,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(pass_waves_p
   const Seg<PassArgs>* s = group_seg(segs);
   if (!s) return;
   const PassArgs a = s->a;
-  pass_body<R, MULTI, WU, NT, KIND>(a, lds, blockIdx.x, s->gx);
+  pass_body<R, MULTI, WU, NT, KIND, false>(a, lds, blockIdx.x, s->gx);
 }
 
 // The pass kernel on 16-bit block-scaled storage: the same tiles, phases,
@@ -544,6 +567,15 @@ static void pick_pass16(Launch* L, int store, int kind) {
   }
 }
 
+constexpr uint64_t kStreamBytes = 2ull << 30;  // (see hbm_get)
+
+template <int NT>
+static void pick_stream(Launch* L, int kind) {
+  L->fn = kind == 1 ? reinterpret_cast<const void*>(&k_pass<4, false, true, NT, 1, true>)
+                    : reinterpret_cast<const void*>(&k_pass<4, false, true, NT, 0, true>);
+  L->gfn = nullptr;
+}
+
 // Block shape of a pass: one 2^(R+9)-entry tile per 512-thread block, one
 // 2^(R+8)-entry tile per 256-thread block, or several smaller tiles per
 // 256-thread block (their waves lie inside one tile when T - R >= 6).
@@ -572,6 +604,14 @@ static hipError_t record_pass_r(const PassArgs& a, Launch* L) {
   } else {
     if (s16) pick_pass16<R, kBlock, true, false>(L, a.store, a.kind);
     else pick_pass<R, kBlock, true, false>(L, a.kind);
+  }
+  // streaming tensors (whole tiles per block; never merged with others' launches)
+  const bool runs = a.lo_bits == 0 || (sizeof(float2) << a.lo_bits) >= 128;
+  if constexpr (R == 4) {
+    if (!s16 && !multi && runs && ((uint64_t)a.n_tiles << (a.T + 3)) >= kStreamBytes) {
+      if (NT == 512) pick_stream<512>(L, a.kind);
+      else pick_stream<kBlock>(L, a.kind);
+    }
   }
   set_arg(L, a);
   return set_shape(L, blocks, 1, NT, lds);
