@@ -870,8 +870,8 @@ void emulate_pass_host(const PassArgs& a, int R) {
 // very uneven: one amplitude per batch sums thousands of products into one
 // value, eight open legs are a square 256-column product.  Three kernels
 // share the work (record_late):
-//   k_late_mf   N >= 16: tiles on the FP64 matrix cores
-//   k_late_dot  N < 16, or few rows, with K >= 64: lanes along K
+//   k_late_mf   N >= 4: tiles on the FP64 matrix cores
+//   k_late_dot  N < 4, or few rows, with K >= 64: lanes along K
 //   k_late_out  K < 64 otherwise: a thread per output
 __device__ inline double2 to_d2(float2 v) { return make_double2((double)v.x, (double)v.y); }
 __device__ inline double2 to_d2(double2 v) { return v; }
@@ -1147,14 +1147,18 @@ static void pick_late_dot(Launch* L) {
   if (S == STORE_C64) L->gfn = reinterpret_cast<const void*>(&k_late_dot_g<TIn, S, NC, RB>);
 }
 
-// The kernel and grid of a first late launch.  16 columns or more, a K of one
-// MFMA slice and at least 64 rows fill the matrix-core tiles; below that the
-// lanes go along K where K gives every lane of a wave a product, and else a
-// thread computes one output.  RB rows share a read of J: as many as leave
-// one sum per lane, no more than eight.
+// The kernel and grid of a first late launch.  16 columns, a K of one MFMA
+// slice and at least 64 rows fill the matrix-core tiles.  With eight or four
+// columns (two, below 256 products) a tile's padding still costs less than
+// lanes along K, whose sums meet after one product each when K is 64: join and
+// late launches of 3 x 2^27 entries, 8 columns, 3.7 ms in 64-column vector
+// tiles, about 20 ms along K, 1.4 ms here; of 2^30 entries, 2 columns, 14.9,
+// 21.4 and 5.0 ms.  Below that the lanes go along K where K gives every lane
+// of a wave a product, and else a thread computes one output.  RB rows share a read of J: as many as leave one sum
+// per lane, no more than eight.
 template <typename TIn, int S>
 static long long pick_late(const LateArgs& a, Launch* L) {
-  if (a.N >= 16 && a.K >= 16 && a.M >= 64) {
+  if ((a.N >= 4 || (a.N == 2 && a.K >= 64 && a.K < 256)) && a.K >= 16 && a.M >= 64) {
     const int CT = a.N >= 64 ? 64 : a.N >= 32 ? 32 : 16;
     const int RT = CT == 64 ? 64 : 128;
     if (CT == 64) pick_late_mf<TIn, S, 64>(L);

@@ -43,6 +43,8 @@ CASES = [
     (9, 26, 5, 2, 2),
     (9, 24, 6, -1, 2),    # the 64-column tile
     (9, 20, 5, 1, 2),     # N = 32, 16 rows: K = 64
+    (9, 26, 1, 7, 2),     # N = 2, K = 256 and 32 rows
+    (9, 25, 1, 5, 2),     # N = 2, K = 64: 64 rows or more on the matrix cores
 ]
 
 
