@@ -300,7 +300,9 @@ int tnc_profile_launches(int32_t* cls, double* ms, int64_t cap, int64_t* n);
 /* The HBM passes of the fixed sweep for k open legs, in launch order: seven
  * int32 per pass, {low slots, window start, window length, register bits,
  * updates, register phases, fused phases}; *n_passes = their number, at most
- * cap are written.  Host only. */
+ * cap are written.  Complex64 calls of a plan without tile options run the same
+ * updates over tiles chosen by size instead (small ones in one launch), with the
+ * same results.  Host only. */
 int tnc_plan_passes(tnc_plan_t plan, int32_t k, int32_t* out, int32_t cap, int32_t* n_passes);
 
 /*
