@@ -91,7 +91,7 @@ typedef struct {
                             reg_bits + 2 updates.  Other values: TNC_E_INVALID */
   int32_t late_fold;     /* k >= 1: late removals folded into the join launch (0:
                             automatic, 7 for boundary tensors of 2^35 entries, 5 for
-                            2^30 or more, 3 for 2^26 or more or for calls of 2^23
+                            2^30 or more, 3 for 2^26 or more or for calls of 2^24
                             entries together, else none; -1: none; 1..8: that many) */
   int32_t reg_adapt;     /* 1: a pass takes reg_bits - 1 when that needs no more register
                             phases and its tile fits 256 threads (more resident waves);

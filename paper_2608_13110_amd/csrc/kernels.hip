@@ -1036,10 +1036,11 @@ __device__ __attribute__((always_inline)) inline void late_mf_body(const LateArg
   // Consecutive block ids go to different XCDs (round robin over 8); the
   // tilesN column blocks of one row tile are given ids that land on the
   // same XCD, so they share its L2 for the row tile.
+  // (with fewer than eight row tiles that would leave XCDs idle: in order)
   const int xcd = bx & 7;
   const int g = bx >> 3;
-  const int bn = g % tilesN;
-  const int bm = (g / tilesN) * 8 + xcd;
+  const int bn = tilesM < 8 ? bx % tilesN : g % tilesN;
+  const int bm = tilesM < 8 ? bx / tilesN : (g / tilesN) * 8 + xcd;
   if (bm >= tilesM) return;
   const int row0 = bm * RT, col0 = bn * CT;
   const int var = a.xrow >= 0 ? (int)a.bits[(size_t)b * a.n + a.xrow] : 0;
@@ -1164,7 +1165,8 @@ static long long pick_late(const LateArgs& a, Launch* L) {
     if (CT == 64) pick_late_mf<TIn, S, 64>(L);
     else if (CT == 32) pick_late_mf<TIn, S, 32>(L);
     else pick_late_mf<TIn, S, 16>(L);
-    return (((long long)a.M + RT - 1) / RT + 7) / 8 * 8 * ((a.N + CT - 1) / CT);
+    const long long tilesM = ((long long)a.M + RT - 1) / RT;
+    return (tilesM < 8 ? tilesM : (tilesM + 7) / 8 * 8) * ((a.N + CT - 1) / CT);
   }
   if (a.K >= 64) {
     const int NC = std::min(a.N, 8);
@@ -1376,7 +1378,7 @@ hipError_t record_late_ops(const LateOpsArgs& a, Launch* L) {
 // ---------------------------------------------------------------------------
 // The join matrix with j late removals folded in, once per plan and k: one row
 // per block, its 2^k-entry state in LDS.  On the host the fold of three removals
-// takes 21 ms at k = 8 and five about 100 ms; here 0.03 ms, so that calls of 2^23
+// takes 21 ms at k = 8 and five about 100 ms; here 0.03 ms, so that calls of 2^24
 // entries have one too.
 __global__ __launch_bounds__(kBlock) void k_fold(const double2* Z, const LateOpDev* src_prog, int n_prog, int k, int j,
                                                  double2* J) {

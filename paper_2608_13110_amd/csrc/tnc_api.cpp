@@ -51,12 +51,12 @@ struct PassHost {
   int R = 5;
 };
 
-// Removals folded into the join of a call of 2^23 entries or more: 2^8 blocks of
+// Removals folded into the join of a call of 2^24 entries or more: 2^9 blocks of
 // the join are left.  The join's flops do not depend on it, its output and the
 // late launches' input shrink eightfold (w = 20, k = 6, 64 batches: join and late
 // launches 1.98 ms without, 0.89 with; w = 24, k = 8: 0.98 and 0.76).
 constexpr int kFoldRemovals = 3;
-bool use_fold(int h, int nb) { return ((uint64_t)nb << h) >= (1ull << 23); }
+bool use_fold(int h, int nb) { return ((uint64_t)nb << h) >= (1ull << 24); }
 
 // A pass of the latency kernel.
 struct WinHost {
@@ -659,7 +659,9 @@ int build_tables(Plan& p, const Schedule& s, HostTables* t, std::string* err) {
   if (p.opt.late_fold == 0 && s.k >= 1 && s.k <= 8 && p.h > kOneMaxBits && t->late.first.j == 0 && !t->late.first.final &&
       t->late.first.N == 1 << s.k && s.n_remove > kFoldRemovals) {
     if ((rc = build_late(p, s, &t->late_folded, err, kFoldRemovals, false))) return rc;
-    t->fold = t->late_folded.first.J.empty();
+    // (at least a tile of 64 rows: fewer leave the matrix cores, w = 15, k = 7 with
+    // 600 batches 1.8 -> 5.3 ms)
+    t->fold = t->late_folded.first.J.empty() && t->late_folded.first.M >= 64;
   }
   for (const LateOp& lo : s.late) {
     LateOpDev d;

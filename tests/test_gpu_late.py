@@ -63,9 +63,9 @@ def test_first_late_launch(n, d, k, fold, nb, storage):
     assert per < (H.TOL_C64 if storage == "c64" else 4e-2), (per, l2)
 
 
-@pytest.mark.parametrize("d,k,nb", [(34, 3, 130), (40, 6, 9), (44, 8, 3), (46, 1, 1), (48, 5, 1), (50, 4, 1), (52, 2, 1)])
+@pytest.mark.parametrize("d,k,nb", [(34, 3, 130), (40, 6, 17), (44, 8, 5), (36, 8, 65), (30, 7, 513), (32, 7, 257), (46, 1, 2), (48, 5, 1), (50, 4, 1), (52, 2, 1)])
 def test_folded_join(d, k, nb):
-    # calls of 2^23 entries or more fold three removals into the join matrix on
+    # calls of 2^24 entries or more fold three removals into the join matrix on
     # the device, from 2^26 entries on (and 2^25 with the option) so does the
     # plan's own join: against the late phase without a fold (FP64 both: 1e-12)
     # and the oracle
