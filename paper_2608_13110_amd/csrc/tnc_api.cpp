@@ -1629,7 +1629,8 @@ int tnc_plan_info(tnc_plan_t plan, int32_t k, tnc_info* info) {
   info->live_slots_fixed = s->m_fix;
   info->n_ops = (int32_t)std::count_if(s->ops.begin(), s->ops.end(), [](const SweepOp& o) { return o.kind != OP_D4H; });
   info->n_passes = (int32_t)s->passes.size();
-  info->n_phases = (int32_t)t.phases.size();
+  info->n_phases = 0;
+  for (const Pass& ps : s->passes) info->n_phases += (int32_t)ps.phases.size();  // (t.phases also holds sized's)
   info->n_late_launches = 1 + (int32_t)t.late.ops.size();
   info->fixed_rows = s->last_fixed_row + 1;
   info->early_layers = k >= 1 ? 2 * k : 0;
