@@ -569,11 +569,13 @@ static void pick_pass16(Launch* L, int store, int kind) {
 
 constexpr uint64_t kStreamBytes = 2ull << 30;  // (see hbm_get)
 
+// The streaming form of a pass that pick_pass chose: the same updates, and its
+// grouped entry point stays the one without marks (a launch without one could not
+// stand in a group, not even alone).
 template <int NT>
 static void pick_stream(Launch* L, int kind) {
   L->fn = kind == 1 ? reinterpret_cast<const void*>(&k_pass<4, false, true, NT, 1, true>)
                     : reinterpret_cast<const void*>(&k_pass<4, false, true, NT, 0, true>);
-  L->gfn = nullptr;
 }
 
 // Block shape of a pass: one 2^(R+9)-entry tile per 512-thread block, one
@@ -605,7 +607,7 @@ static hipError_t record_pass_r(const PassArgs& a, Launch* L) {
     if (s16) pick_pass16<R, kBlock, true, false>(L, a.store, a.kind);
     else pick_pass<R, kBlock, true, false>(L, a.kind);
   }
-  // streaming tensors (whole tiles per block; never merged with others' launches)
+  // streaming tensors (whole tiles per block)
   const bool runs = a.lo_bits == 0 || (sizeof(float2) << a.lo_bits) >= 128;
   if constexpr (R == 4) {
     if (!s16 && !multi && runs && ((uint64_t)a.n_tiles << (a.T + 3)) >= kStreamBytes) {

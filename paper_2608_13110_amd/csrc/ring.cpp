@@ -207,7 +207,8 @@ int tnc_ring_amplitudes(tnc_ring_plan_t ring, int32_t n_batches, const uint8_t* 
     uint64_t seg_at = 0;
     for (size_t j = 0; j < ls[0].size(); ++j) {
       for (int i = 0; i < G; ++i) {
-        if (!tnc::groupable(ls[0][j], ls[i][j])) return ring_err(TNC_E_INVALID, "ring slices of different launches");
+        // (a slice by itself is issued as it was recorded, whatever its kernels)
+        if (G >= 2 && !tnc::groupable(ls[0][j], ls[i][j])) return ring_err(TNC_E_INVALID, "ring slices of different launches");
         steps[j].push_back(&ls[i][j]);
       }
       if (G < 2) continue;

@@ -51,3 +51,29 @@ def test_ring_equals_host_emulation_of_its_slices():
     emu = rp.debug_emulate_device(bits, 2)
     per, l2 = H.amp_errors(got, emu, 10)
     assert per < 1e-6
+
+
+@pytest.mark.parametrize("d,k,nb,opts", [
+    (44, 2, 64, None),                              # 2^22 entries: the passes over the lowest slots stream
+    (52, 3, 4, None),                               # 2^26: every pass, 256 threads a tile
+    (56, 1, 1, None),                               # 2^28: 512 threads
+    (52, 2, 4, dict(reg_bits=4, math=2)),           # fused phases
+    (30, 2, 1 << 13, dict(max_tile_bits=13, reg_bits=4))])
+def test_ring_of_slices_of_two_gib(d, k, nb, opts):
+    # slices of 2 GiB run one by one, with the passes whose lines are not kept
+    import dataclasses
+    from paper_2608_13110_amd import RingPlan
+    n = 10
+    c = H.mixed_circuit(n, d, d, dense=0.3)
+    wrap = [(layer, n - 1, W.GATE_CZ, None) for layer in range(1, d + 1) if W.brickwork_pairs(n, layer, 1)[:1] == [1]]
+    c = dataclasses.replace(c, gates=sorted(list(c.gates) + wrap[3:5], key=lambda g: (g[0], g[1])))
+    bits = W.random_bitstrings(n, nb, W.rng_for(143, d))
+    rp = RingPlan.from_circuit(c, opts)
+    info = rp.info(k, nb)
+    print(f"  [gpu] ring n={n} d={d} k={k} batches={nb}: {info}", flush=True)
+    assert info["slices"] == 4 and info["workspace_bytes"] >= 2 << 30
+    got = rp.amplitudes(torch.from_numpy(bits).cuda(), k)
+    torch.cuda.synchronize()
+    per, l2 = H.amp_errors(got.cpu().numpy(), oracle.amplitudes(c, bits, k), n)
+    assert per < H.TOL_C64 and l2 < H.TOL_C64, (per, l2)
+    rp.close()
