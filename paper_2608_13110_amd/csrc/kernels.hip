@@ -2136,7 +2136,8 @@ __device__ inline double2 xeb_block_sums(const double2* amps, int k, const int32
   return make_double2(s1[0], s2[0]);
 }
 
-// One block: up to 1024 components by 256 threads, up to kXebSingle by 1024.
+// One block: up to 1024 components by 256 threads, up to kXebSingle by 1024 (8192
+// components 11.6 us with 256 threads, 8.5 with 1024).
 template <int NT>
 __global__ __launch_bounds__(NT) void k_logxeb(const double2* amps, long long total, int k, const int32_t* sel,
                                                    int n_qubits, double* result) {
@@ -2150,9 +2151,19 @@ __global__ __launch_bounds__(NT) void k_logxeb(const double2* amps, long long to
 // hi * q + lo * q / 2^40, q a power of two that keeps the total below 2^62.
 // Integer sums do not depend on the order of arrival, so the result is the
 // same from run to run, and their 100 bits add no rounding of note.  One block
-// computes 2051 x 256 logarithms in 780 us (one CU), 128 blocks in 17 us.
+// of 256 computes 2051 x 256 logarithms in 780 us (one CU), 128 blocks in 17 us.
 constexpr int kXebBlocks = 128;  // (their sums meet at five addresses: 512 blocks took 37 us)
-constexpr long long kXebSingle = 8192;  // up to here one block of 1024 is as fast and needs no clearing launch
+// Up to here one block of 1024 threads.  The clearing launch costs the host 2.5
+// us, which is what a call costs among others that it waits for.  us per call,
+// one block of 256 / one of 1024 / clearing and many blocks:
+//   components   calls of log-XEB alone   two of them with both samplers
+//         8200   12.0 /  8.6 /  9.6       33.3 / 34.8 / 37.1
+//        10240   13.8 / 10.0 /  9.8       33.5 / 34.6 / 37.5
+//        20480   25.1 / 17.3 /  9.8       34.8 / 34.9 / 37.9
+//        24576   29.6 / 20.1 / 10.0       39.2 / 35.0 / 38.0
+// so the many blocks start where the estimators' sequence, on one block of 256,
+// would have taken as long as with the second launch.
+constexpr long long kXebSingle = 20480;
 static_assert(kXebBlocks < (1 << 12), "arrival fields of 16 bits, low words of 40 bits");
 
 // ln p of a finite nonzero double lies in (-746, 710): |sum| < total 2^10 and

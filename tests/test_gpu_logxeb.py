@@ -52,3 +52,15 @@ def test_logxeb_special_values(nb, value, want):
     got = logxeb(torch.from_numpy(z).cuda(), 0, 59).cpu().numpy()
     assert got[0] == want or (math.isnan(want) and math.isnan(got[0]))
     assert got[1] == 0.0 and got[4] == nb
+
+
+@pytest.mark.parametrize("nb,k,select", [(20480, 0, False), (20480, 2, True), (20481, 0, False), (20481, 3, True), (5121, 2, False)])
+def test_logxeb_where_blocks_take_over(nb, k, select):
+    # 20480 components end the single block
+    test_logxeb_sizes(nb, k, select)
+
+
+@pytest.mark.parametrize("value,want", [(0.0, -math.inf), (math.inf, math.inf), (math.nan, math.nan)])
+@pytest.mark.parametrize("nb", [20481, 60000])
+def test_logxeb_special_values_over_blocks(nb, value, want):
+    test_logxeb_special_values(nb, value, want)
