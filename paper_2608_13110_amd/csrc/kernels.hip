@@ -872,8 +872,8 @@ void emulate_pass_host(const PassArgs& a, int R) {
 // very uneven: one amplitude per batch sums thousands of products into one
 // value, eight open legs are a square 256-column product.  Three kernels
 // share the work (record_late):
-//   k_late_mf   N >= 4: tiles on the FP64 matrix cores
-//   k_late_dot  N < 4, or few rows, with K >= 64: lanes along K
+//   k_late_mf   N >= 4 and 64 rows: tiles on the FP64 matrix cores
+//   k_late_dot  fewer of either, with K >= 64: lanes along K
 //   k_late_out  K < 64 otherwise: a thread per output
 __device__ inline double2 to_d2(float2 v) { return make_double2((double)v.x, (double)v.y); }
 __device__ inline double2 to_d2(double2 v) { return v; }
@@ -899,19 +899,27 @@ __device__ inline double2 late_in(const LateArgs& a, const TIn* __restrict__ in,
 // entries of a bond-four circuit of 26 layers (256 MiB), against 7 us and 121 us
 // (2.2 TB/s) here.  Conditional loads of the rows past M made the compiler wait
 // on each (177 us).
+// (one function per halving, so that every index is a constant: as a loop over h
+// it was not unrolled at V = 32, and the sums went to scratch memory)
+template <int H, int Mask, int V>
+__device__ __attribute__((always_inline)) inline void lane_halve(double (&v)[V], int lane) {
+  if constexpr (H >= 1) {
+    const bool up = (lane & Mask) != 0;
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      const double send = up ? v[i] : v[i + H];
+      v[i] = (up ? v[i + H] : v[i]) + __shfl_xor(send, Mask);
+    }
+    lane_halve<H / 2, Mask / 2>(v, lane);
+  } else {
+#pragma unroll
+    for (int mask = Mask; mask >= 1; mask >>= 1) v[0] += __shfl_xor(v[0], mask);
+  }
+}
+
 template <int V>
 __device__ __attribute__((always_inline)) inline double lane_reduce(double (&v)[V], int lane) {
-  int mask = 32;
-#pragma unroll
-  for (int h = V / 2; h >= 1; h >>= 1, mask >>= 1) {
-    const bool up = (lane & mask) != 0;
-#pragma unroll
-    for (int i = 0; i < h; ++i) {
-      const double send = up ? v[i] : v[i + h];
-      v[i] = (up ? v[i + h] : v[i]) + __shfl_xor(send, mask);
-    }
-  }
-  for (; mask >= 1; mask >>= 1) v[0] += __shfl_xor(v[0], mask);
+  lane_halve<V / 2, 32>(v, lane);
   return v[0];
 }
 
@@ -1150,18 +1158,25 @@ static void pick_late_dot(Launch* L) {
   if (S == STORE_C64) L->gfn = reinterpret_cast<const void*>(&k_late_dot_g<TIn, S, NC, RB>);
 }
 
-// The kernel and grid of a first late launch.  16 columns, a K of one MFMA
-// slice and at least 64 rows fill the matrix-core tiles.  With eight or four
-// columns (two, below 256 products) a tile's padding still costs less than
-// lanes along K, whose sums meet after one product each when K is 64: join and
-// late launches of 3 x 2^27 entries, 8 columns, 3.7 ms in 64-column vector
-// tiles, about 20 ms along K, 1.4 ms here; of 2^30 entries, 2 columns, 14.9,
-// 21.4 and 5.0 ms.  Below that the lanes go along K where K gives every lane
-// of a wave a product, and else a thread computes one output.  RB rows share a read of J: as many as leave one sum
-// per lane, no more than eight.
+// The kernel and grid of a first late launch.  At least four columns, a K of one
+// MFMA slice and 64 rows take the matrix-core tiles, padded to 16 columns.  Below
+// that the lanes go along K where K gives every lane of a wave a product, and else
+// a thread computes one output.  us of the join, 16-column tile / along K:
+//   tensor                 2 columns       4 columns       8 columns
+//   2^17 entries, K = 64   18.6 /  7.8     18.4 /  6.8     18.6 /   7.0
+//   2^20, K = 256          67.0 /  9.0     67.2 / 10.1     67.2 /  15.2
+//   2^24, K = 64           64.3 / 51.3     64.4 / 71.4     65.3 / 136.7
+//   2^27, K = 128           604 /  467      604 /  647      619 /  1181
+//   2^27, K = 512           629 /  376      628 /  465      640 /  1035
+// Two columns are faster along K at every size.  With four and eight a single small
+// tensor would be as well, but the rule sees one batch (the groups that a call is
+// split into must not change its results), and of many batches or a large tensor
+// the tiles take half the time.  (A 64-column vector tile: 217 us at 2^24 entries,
+// 1790 at 2^27.)  RB rows share a read of J: as many as leave one sum per lane, no
+// more than eight.
 template <typename TIn, int S>
 static long long pick_late(const LateArgs& a, Launch* L) {
-  if ((a.N >= 4 || (a.N == 2 && a.K >= 64 && a.K < 256)) && a.K >= 16 && a.M >= 64) {
+  if (a.N >= 4 && a.K >= 16 && a.M >= 64) {
     const int CT = a.N >= 64 ? 64 : a.N >= 32 ? 32 : 16;
     const int RT = CT == 64 ? 64 : 128;
     if (CT == 64) pick_late_mf<TIn, S, 64>(L);
