@@ -1982,10 +1982,11 @@ hipError_t launch_fill_zero(double2* out, long long count, hipStream_t s) {
 }
 
 // out[i] += sum over r < rows of in[r * stride + i] (FP64).  A block takes W
-// consecutive outputs (W = 16, or fewer for a few): thread (g, i) sums rows g, g
-// + 256 / W, ..., and the groups' sums meet in LDS, in a fixed order.  One
-// thread per output, all rows in turn, left 16 threads to read 1024 rows: 240
-// us, 6 us here.
+// consecutive outputs: thread (g, i) sums rows g, g + 256 / W, ..., and the
+// groups' sums meet in LDS, in a fixed order.  One thread per output, all rows in
+// turn, left 16 threads to read 1024 rows: 240 us, 6 us here with W = 16.  With
+// fewer rows than groups the idle threads would cost more than the chain, so W
+// grows until every group has a row (launch_accumulate_rows).
 __global__ __launch_bounds__(kBlock) void k_accumulate_rows(double2* out, const double2* in, long long stride,
                                                            int rows, long long count, int W) {
   __shared__ double2 part[kBlock];
@@ -2018,8 +2019,8 @@ __global__ __launch_bounds__(kBlock) void k_accumulate_rows(double2* out, const 
 hipError_t launch_accumulate_rows(double2* out, const double2* in, long long stride, int rows, long long count,
                                   hipStream_t s) {
   if (count <= 0 || rows <= 0) return hipSuccess;
-  int W = 1;
-  while (W < 16 && W < count) W *= 2;
+  int W = kBlock;
+  while (W > 1 && (W / 2 >= count || (W > 16 && kBlock / W < rows))) W /= 2;
   return launch_direct(reinterpret_cast<const void*>(&k_accumulate_rows), dim3((unsigned)((count + W - 1) / W)),
                        dim3(kBlock), s, out, in, stride, rows, count, W);
 }

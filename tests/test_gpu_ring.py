@@ -77,3 +77,23 @@ def test_ring_of_slices_of_two_gib(d, k, nb, opts):
     per, l2 = H.amp_errors(got.cpu().numpy(), oracle.amplitudes(c, bits, k), n)
     assert per < H.TOL_C64 and l2 < H.TOL_C64, (per, l2)
     rp.close()
+
+
+@pytest.mark.parametrize("wraps,k,nb", [(1, 0, 1), (1, 3, 3), (2, 0, 33), (2, 3, 100), (3, 2, 67), (4, 0, 5), (5, 3, 31), (6, 1, 9)])
+def test_sum_of_few_slices(wraps, k, nb):
+    # 2 to 64 slices, with fewer outputs than a block takes, as many, and more
+    import dataclasses
+    from paper_2608_13110_amd import RingPlan
+    n, d = 10, 14
+    c = H.mixed_circuit(n, d, wraps, dense=0.3)
+    wrap = [(layer, n - 1, W.GATE_CZ, None) for layer in range(1, d + 1) if W.brickwork_pairs(n, layer, 1)[:1] == [1]]
+    c = dataclasses.replace(c, gates=sorted(list(c.gates) + wrap[:wraps], key=lambda g: (g[0], g[1])))
+    bits = W.random_bitstrings(n, nb, W.rng_for(144, wraps))
+    rp = RingPlan.from_circuit(c)
+    assert rp.info(k, nb)["slices"] == 1 << wraps
+    print(f"  [gpu] ring n={n} d={d} k={k} batches={nb} slices={1 << wraps}", flush=True)
+    got = rp.amplitudes(torch.from_numpy(bits).cuda(), k)
+    torch.cuda.synchronize()
+    per, l2 = H.amp_errors(got.cpu().numpy(), oracle.amplitudes(c, bits, k), n)
+    assert per < H.TOL_C64 and l2 < H.TOL_C64, (per, l2)
+    rp.close()
