@@ -990,38 +990,43 @@ __global__ __launch_bounds__(kBlock) void k_late_dot_g(const Seg<LateArgs>* __re
   late_dot_body<TIn, S, NC, RB>(a, blockIdx.x, blockIdx.y);
 }
 
-// One thread per output: with K < 64 a row and J's columns stay in the L1
-// cache, neighbouring threads share a row's entries and read J in runs.
+// One thread per output (of more than kLateOutBlocks blocks' threads: every so
+// many): with K < 64 a row and J's columns stay in the L1 cache, neighbouring
+// threads share a row's entries and read J in runs.
+constexpr long long kLateOutBlocks = 1 << 23;  // 2^31 threads: a launch has to stay below 2^32
 template <typename TIn, int S>
-__device__ __attribute__((always_inline)) inline void late_out_body(const LateArgs& a, uint32_t bx, uint32_t by) {
+__device__ __attribute__((always_inline)) inline void late_out_body(const LateArgs& a, uint32_t bx, uint32_t by,
+                                                                    uint32_t gx) {
   const int b = by;
-  const long long o = (long long)bx * kBlock + threadIdx.x;
-  if (o >= (long long)a.M * a.N) return;
-  const int col = (int)(o % a.N);
-  const uint64_t row = (uint64_t)(o / a.N);
   const int var = a.xrow >= 0 ? (int)(a.bits[(size_t)b * a.n + a.xrow] & 1) : 0;
-  const double2* __restrict__ J = a.J + (size_t)var * a.K * a.N + col;
   const TIn* __restrict__ in = reinterpret_cast<const TIn*>(a.in) + (size_t)b * a.in_batch_stride;
-  double2 acc = make_double2(0.0, 0.0);
+  for (long long o = (long long)bx * kBlock + threadIdx.x; o < (long long)a.M * a.N; o += (long long)gx * kBlock) {
+    const int col = (int)(o % a.N);
+    const uint64_t row = (uint64_t)(o / a.N);
+    const double2* __restrict__ J = a.J + (size_t)var * a.K * a.N + col;
+    double2 acc = make_double2(0.0, 0.0);
 #pragma unroll 8
-  for (int kk = 0; kk < a.K; ++kk) {
-    const double2 x = late_in<TIn, S>(a, in, b, row * a.K + kk);
-    const double2 z = J[(size_t)kk * a.N];
-    acc.x += x.x * z.x - x.y * z.y;
-    acc.y += x.x * z.y + x.y * z.x;
+    for (int kk = 0; kk < a.K; ++kk) {
+      const double2 x = late_in<TIn, S>(a, in, b, row * a.K + kk);
+      const double2 z = J[(size_t)kk * a.N];
+      acc.x += x.x * z.x - x.y * z.y;
+      acc.y += x.x * z.y + x.y * z.x;
+    }
+    a.out[(size_t)b * a.out_batch_stride + o] = acc;
   }
-  a.out[(size_t)b * a.out_batch_stride + o] = acc;
 }
 
 template <typename TIn, int S>
-__global__ __launch_bounds__(kBlock) void k_late_out(LateArgs a) { late_out_body<TIn, S>(a, blockIdx.x, blockIdx.y); }
+__global__ __launch_bounds__(kBlock) void k_late_out(LateArgs a) {
+  late_out_body<TIn, S>(a, blockIdx.x, blockIdx.y, gridDim.x);
+}
 
 template <typename TIn, int S>
 __global__ __launch_bounds__(kBlock) void k_late_out_g(const Seg<LateArgs>* __restrict__ segs) {
   const Seg<LateArgs>* s = group_seg(segs);
   if (!s) return;
   const LateArgs a = s->a;
-  late_out_body<TIn, S>(a, blockIdx.x, blockIdx.y);
+  late_out_body<TIn, S>(a, blockIdx.x, blockIdx.y, s->gx);
 }
 
 // The same contraction on the FP64 matrix cores (v_mfma_f64_16x16x4f64):
@@ -1197,7 +1202,7 @@ static long long pick_late(const LateArgs& a, Launch* L) {
   }
   L->fn = reinterpret_cast<const void*>(&k_late_out<TIn, S>);
   if (S == STORE_C64) L->gfn = reinterpret_cast<const void*>(&k_late_out_g<TIn, S>);
-  return ((long long)a.M * a.N + kBlock - 1) / kBlock;
+  return std::min(kLateOutBlocks, ((long long)a.M * a.N + kBlock - 1) / kBlock);
 }
 
 hipError_t record_late(const LateArgs& a, bool in_c64, Launch* L) {

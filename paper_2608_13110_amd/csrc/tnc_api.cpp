@@ -1156,9 +1156,15 @@ int record_launches(Plan& p, DevSched& ds, int nb_total, const uint8_t* d_bits, 
   out->clear();
   Launch rec;
   if (t.one && !s16) {
-    const OneArgs a = one_args(p, ds, nb_total, d_bits, k, reinterpret_cast<double2*>(d_out));
-    if (record_one(a, &rec) != hipSuccess) return shape_err("one launch");
-    out->push_back(rec);
+    // (a block per batch, at most 512 threads: a launch has to stay below 2^32)
+    constexpr int kOneBatches = 1 << 22;
+    for (int b0 = 0; b0 < nb_total; b0 += kOneBatches) {
+      const OneArgs a = one_args(p, ds, std::min(kOneBatches, nb_total - b0), d_bits + (size_t)b0 * p.n, k,
+                                 reinterpret_cast<double2*>(d_out) + ((size_t)b0 << k));
+      if (record_one(a, &rec) != hipSuccess) return shape_err("one launch");
+      out->push_back(rec);
+      if (nb_total - b0 <= kOneBatches) break;
+    }
     return TNC_OK;
   }
   for (int b0 = 0; b0 < nb_total; b0 += chunk) {
