@@ -410,13 +410,25 @@ const char* tnc_last_error(void);
 /*
  * Planner self-checks, host only, FP64 (tests; the device path never calls
  * them).  execute_host runs the plan's own update tables on the host;
- * emulate_device runs the device tables through a host emulation of the
- * pass kernel's thread / LDS mapping, with the given storage mode.
+ * emulate_device runs the tables of the plan's own passes (tnc_plan_passes)
+ * through a host emulation of the pass kernel's thread / LDS mapping, with the
+ * given storage mode.
  * Width <= 24.
  */
 int tnc_debug_execute_host(tnc_plan_t plan, int32_t n_batches, const uint8_t* bits, int32_t k, tnc_c128* out);
 int tnc_debug_emulate_device(tnc_plan_t plan, int32_t n_batches, const uint8_t* bits, int32_t k, int32_t storage,
                              tnc_c128* out);
+
+/* The same emulation (complex64) along a route that calls of the plan take in
+ * place of its own passes and late phase.  TNC_E_DOMAIN: no call of this plan with
+ * these open legs takes it. */
+#define TNC_ROUTE_OWN 0     /* the plan's own passes and late phase (emulate_device) */
+#define TNC_ROUTE_SIZED 1   /* passes over tiles chosen by the tensor's size */
+#define TNC_ROUTE_LATENCY 2 /* the latency kernel's passes (2^13 to 2^20 entries) */
+#define TNC_ROUTE_ONE 3     /* the phases of the one-launch kernel (up to 2^12 entries) */
+#define TNC_ROUTE_FOLDED 4  /* own passes, three late removals folded into the join */
+int tnc_debug_emulate_route(tnc_plan_t plan, int32_t n_batches, const uint8_t* bits, int32_t k, int32_t route,
+                            tnc_c128* out);
 
 /*
  * Complex128 reference path (tests and the accuracy report; not tuned): the

@@ -32,6 +32,8 @@ GATE_DENSE4 = 1
 STORE_C64 = 0
 STORE_F16_BLOCKSCALE = 1
 STORE_BF16_BLOCKSCALE = 2
+# routes of debug_emulate_route
+ROUTE_OWN, ROUTE_SIZED, ROUTE_LATENCY, ROUTE_ONE, ROUTE_FOLDED = range(5)
 
 EXPORTED = [
     "tnc_plan", "tnc_plan_info", "tnc_prepare", "tnc_workspace_bytes", "tnc_amplitudes",
@@ -41,7 +43,7 @@ EXPORTED = [
     "tnc_server_wait", "tnc_server_summary", "tnc_debug_arena_check", "tnc_sample_batched", "tnc_frugal_accept",
     "tnc_plan_ring", "tnc_ring_info", "tnc_ring_amplitudes", "tnc_debug_ring_emulate", "tnc_ring_release",
     "tnc_amplitudes_noalloc", "tnc_noalloc_scratch_bytes", "tnc_debug_workspace_c128", "tnc_debug_amplitudes_c128",
-    "tnc_debug_lds_conflicts", "tnc_profile_launches", "tnc_plan_passes",
+    "tnc_debug_lds_conflicts", "tnc_profile_launches", "tnc_plan_passes", "tnc_debug_emulate_route",
 ]
 
 
@@ -159,6 +161,7 @@ def lib() -> ctypes.CDLL:
     L.tnc_last_error.restype = ctypes.c_char_p
     L.tnc_debug_execute_host.argtypes = [vp, i32, vp, i32, vp]
     L.tnc_debug_emulate_device.argtypes = [vp, i32, vp, i32, i32, vp]
+    L.tnc_debug_emulate_route.argtypes = [vp, i32, vp, i32, i32, vp]
     L.tnc_profile_begin.argtypes = []
     L.tnc_profile_end.argtypes = [ctypes.POINTER(Profile)]
     L.tnc_autotune.argtypes = [i32, i32, i32, i32, vp, i32, i32, ctypes.POINTER(i32), vp]
@@ -358,6 +361,14 @@ class Plan:
         out = np.empty((bits.shape[0], 1 << k), dtype=np.complex128)
         _check(lib().tnc_debug_emulate_device(self._h, bits.shape[0], bits.ctypes.data, int(k), int(storage),
                                               out.ctypes.data))
+        return out
+
+    def debug_emulate_route(self, bits: np.ndarray, k: int, route: int) -> np.ndarray:
+        """Host emulation along one of the routes that calls take (``tnc_debug_emulate_route``)."""
+        bits = np.ascontiguousarray(bits, dtype=np.uint8)
+        out = np.empty((bits.shape[0], 1 << k), dtype=np.complex128)
+        _check(lib().tnc_debug_emulate_route(self._h, bits.shape[0], bits.ctypes.data, int(k), int(route),
+                                             out.ctypes.data))
         return out
 
 

@@ -864,6 +864,54 @@ void emulate_pass_host(const PassArgs& a, int R) {
   }
 }
 
+// Host emulation of the phases that the one-launch and latency kernels run on a
+// tile in LDS (LDS order), thread by thread: the addresses and control bit that
+// one_thread and one_fetch look up, the updates of one_step and one_rest.
+template <int R>
+static void emulate_one_r(const OnePhase* phases, const OneSlot* slots, int n_phases, const float* mats,
+                          const uint8_t* bits, int T, char* tile) {
+  for (int p = 0; p < n_phases; ++p) {
+    const OnePhase& P = phases[p];
+    const float* m[R] = {};
+    for (int b = 0; b < P.n_ops; ++b) {
+      const OneSlot& s = slots[p * R + b];
+      const int var = (s.xrow0 >= 0 ? 2 * (bits[s.xrow0] & 1) : 0) + (s.xrow1 >= 0 ? (bits[s.xrow1] & 1) : 0);
+      m[b] = mats + ((size_t)s.op * 4 + var) * 16;
+    }
+    for (uint32_t tt = 0; tt < (1u << (T - R)); ++tt) {
+      const uint32_t vb = P.low[tt & 15u] ^ P.high[tt >> 4];
+      Regs<R> v;
+      for (int i = 0; i < (1 << R); ++i) {
+        const float2 x = *reinterpret_cast<const float2*>(tile + ((vb & ~kOneCtl) ^ P.off[i]));
+        v.x[i] = x.x;
+        v.y[i] = x.y;
+      }
+      v = op_sel<R, 0>(v, m[0] + 8 * (vb >> 31));
+      if constexpr (R > 1)
+        if (P.n_ops > 1) v = op_reg<R, 1, 0>(v, m[1]);
+      if constexpr (R > 2)
+        if (P.n_ops > 2) v = op_reg<R, 2, 1>(v, m[2]);
+      for (int i = 0; i < (1 << R); ++i)
+        *reinterpret_cast<float2*>(tile + ((vb & ~kOneCtl) ^ P.off[i])) = make_float2(v.x[i], v.y[i]);
+    }
+  }
+}
+
+void emulate_one_host(const OnePhase* phases, const OneSlot* slots, int n_phases, const float* mats,
+                      const uint8_t* bits, float2* B, int T, int R, int lo_bits, int win_lo, uint64_t boff) {
+  std::vector<float2> tile(size_t(1) << T);
+  auto at = [&](uint32_t i) -> float2& { return B[boff + tile_offset(i, lo_bits, win_lo)]; };
+  for (uint32_t i = 0; i < (1u << T); ++i) tile[swz(i)] = at(i);
+  char* t = reinterpret_cast<char*>(tile.data());
+  switch (R) {
+    case 1: emulate_one_r<1>(phases, slots, n_phases, mats, bits, T, t); break;
+    case 2: emulate_one_r<2>(phases, slots, n_phases, mats, bits, T, t); break;
+    case 3: emulate_one_r<3>(phases, slots, n_phases, mats, bits, T, t); break;
+    default: break;
+  }
+  for (uint32_t i = 0; i < (1u << T); ++i) at(i) = tile[swz(i)];
+}
+
 // ---------------------------------------------------------------------------
 // Late phase: out[b][r][c] = sum_kk in[b][r][kk] * J[var][kk][c] in FP64.
 // J folds the early-region tensor Z_early (first launch), the late layers'

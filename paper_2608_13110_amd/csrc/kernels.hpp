@@ -720,5 +720,9 @@ hipError_t launch_logxeb(const double2* amps, int n_batches, int k, const int32_
 
 // Host emulation of the pass kernel (exact thread / LDS mapping), for tests.
 void emulate_pass_host(const PassArgs& a, int R);
+// The same of the one-launch and latency kernels' phases, on one 2^T-entry tile of
+// a batch's tensor B (entry i at boff + tile_offset(i, lo_bits, win_lo)).
+void emulate_one_host(const OnePhase* phases, const OneSlot* slots, int n_phases, const float* mats,
+                      const uint8_t* bits, float2* B, int T, int R, int lo_bits, int win_lo, uint64_t boff);
 
 }  // namespace tnc

@@ -1365,8 +1365,9 @@ int run_c128(Plan& p, DevSched& ds, int nb_total, const uint8_t* d_bits, int k, 
   return TNC_OK;
 }
 
-// Host emulation of the whole device pipeline with the same tables.
-int emulate(Plan& p, int k, int nb, const uint8_t* bits, int storage, cd* out) {
+// Host emulation of the whole device pipeline with the same tables, along one of
+// the routes that a call may take (TNC_ROUTE_*).
+int emulate(Plan& p, int k, int nb, const uint8_t* bits, int storage, int route, cd* out) {
   std::shared_ptr<Schedule> s;
   std::string err;
   int rc = get_schedule(p, k, &s, &err);
@@ -1377,6 +1378,14 @@ int emulate(Plan& p, int k, int nb, const uint8_t* bits, int storage, cd* out) {
   if (p.h > 24) return set_err(TNC_E_DOMAIN, "emulation limited to width 24");
   if ((rc = check_storage(t, storage))) return rc;
   const bool s16 = is_s16(storage);
+  if ((route == TNC_ROUTE_SIZED && t.sized.empty()) || (route == TNC_ROUTE_LATENCY && t.wins.empty()) ||
+      (route == TNC_ROUTE_ONE && !t.one) || (route == TNC_ROUTE_FOLDED && !t.fold) || route < 0 ||
+      route > TNC_ROUTE_FOLDED || (s16 && route != TNC_ROUTE_OWN && route != TNC_ROUTE_FOLDED))
+    return set_err(TNC_E_DOMAIN, "no call of this plan takes that route");
+  // (the folded join's matrix is made on the device; here, on the host)
+  LatePlan folded;
+  if (route == TNC_ROUTE_FOLDED && (rc = build_late(p, *s, &folded, &err, kFoldRemovals, true))) return set_err(rc, err);
+  const LatePlan& late = route == TNC_ROUTE_FOLDED ? folded : t.late;
   const size_t dim = size_t(1) << p.h;
   // complex64 tensor, or (16-bit storage) the packed words in its first half
   std::vector<float2> B(dim * nb);
@@ -1426,7 +1435,21 @@ int emulate(Plan& p, int k, int nb, const uint8_t* bits, int storage, cd* out) {
     }
   int cur = 0;
   ScaleMap map = init_map(p);
-  for (const PassHost& ph : t.passes) {
+  for (int b = 0; b < nb && route == TNC_ROUTE_ONE; ++b)
+    emulate_one_host(t.one_phases.data(), t.one_slots.data(), (int)t.one_phases.size(), t.mats.data(),
+                     bits + (size_t)b * p.n, B.data() + (size_t)b * dim, p.h, one_reg_bits(p.h), 0, 0, 0);
+  for (const WinHost& w : t.wins) {
+    if (route != TNC_ROUTE_LATENCY) break;
+    const int T = w.w.tile_bits();
+    for (int tile = 0; tile < nb << (p.h - T); ++tile) {
+      const int b = tile >> (p.h - T);
+      emulate_one_host(t.one_phases.data() + w.phase_off, t.one_slots.data() + w.slot_off, w.n_phases, t.mats.data(),
+                       bits + (size_t)b * p.n, B.data() + (size_t)b * dim, T, w.R, w.w.lo_bits, w.w.win_lo,
+                       block_offset(tile & ((1 << (p.h - T)) - 1), w.w.lo_bits, w.w.win_lo, w.w.win_len));
+    }
+  }
+  for (const PassHost& ph : route == TNC_ROUTE_SIZED ? t.sized : t.passes) {
+    if (route == TNC_ROUTE_ONE || route == TNC_ROUTE_LATENCY) break;
     PassArgs a = pass_args(p, ph, t.phases.data(), t.poffs.data(), t.fmats.empty() ? nullptr : t.fmats.data(), B.data(),
                            bits, nb);
     a.rmats = rmats.data();
@@ -1456,8 +1479,8 @@ int emulate(Plan& p, int k, int nb, const uint8_t* bits, int storage, cd* out) {
     return cd(x.x, x.y);
   };
   // late (FP64), same tables
-  const LateFirst& F = t.late.first;
-  const int sb = t.late.s;
+  const LateFirst& F = late.first;
+  const int sb = late.s;
   for (int b = 0; b < nb; ++b) {
     const int var = F.xrow >= 0 ? bits[(size_t)b * p.n + F.xrow] : 0;
     std::vector<cd> cur((size_t)F.M * F.N);
@@ -1467,7 +1490,7 @@ int emulate(Plan& p, int k, int nb, const uint8_t* bits, int storage, cd* out) {
         for (int kk = 0; kk < F.K; ++kk) acc += entry(b, (uint64_t)r * F.K + kk) * F.J[((size_t)var * F.K + kk) * F.N + c];
         cur[(size_t)r * F.N + c] = acc;
       }
-    for (const LateOpsLaunch& ln : t.late.ops) {
+    for (const LateOpsLaunch& ln : late.ops) {
       const long long rows_out = ln.rows_in >> ln.j;
       std::vector<cd> nxt((size_t)rows_out << sb);
       for (long long ro = 0; ro < rows_out; ++ro) {
@@ -1525,15 +1548,15 @@ int emulate(Plan& p, int k, int nb, const uint8_t* bits, int storage, cd* out) {
     cd* o = out + ((size_t)b << k);
     if (F.final) {
       for (int c = 0; c < (1 << k); ++c) o[c] = cur[c];
-    } else if (t.late.final_kind == L_OUT) {
+    } else if (late.final_kind == L_OUT) {
       for (int bb = 0; bb < (1 << k); ++bb) {
         int tt = 0;
         for (int q = 0; q < k; ++q) tt |= ((bb >> (k - 1 - q)) & 1) << q;
         o[bb] = cur[tt];
       }
     } else {
-      const int x = bits[(size_t)b * p.n + t.late.final_xrow];
-      o[0] = t.late.dot[2 * x] * cur[0] + t.late.dot[2 * x + 1] * cur[1];
+      const int x = bits[(size_t)b * p.n + late.final_xrow];
+      o[0] = late.dot[2 * x] * cur[0] + late.dot[2 * x + 1] * cur[1];
     }
   }
   return TNC_OK;
@@ -1989,7 +2012,18 @@ int tnc_debug_emulate_device(tnc_plan_t plan, int32_t n_batches, const uint8_t* 
   Plan* p = get(plan);
   if (!p || !bits || !out || n_batches < 0) return set_err(TNC_E_INVALID, "bad argument");
   std::vector<cd> o((size_t)n_batches << k);
-  int rc = emulate(*p, k, n_batches, bits, storage, o.data());
+  int rc = emulate(*p, k, n_batches, bits, storage, TNC_ROUTE_OWN, o.data());
+  if (rc) return rc;
+  for (size_t i = 0; i < o.size(); ++i) out[i] = tnc_c128{o[i].real(), o[i].imag()};
+  return TNC_OK;
+}
+
+int tnc_debug_emulate_route(tnc_plan_t plan, int32_t n_batches, const uint8_t* bits, int32_t k, int32_t route,
+                            tnc_c128* out) {
+  Plan* p = get(plan);
+  if (!p || !bits || !out || n_batches < 0 || k < 0 || k > 10) return set_err(TNC_E_INVALID, "bad argument");
+  std::vector<cd> o((size_t)n_batches << k);
+  int rc = emulate(*p, k, n_batches, bits, TNC_STORE_C64, route, o.data());
   if (rc) return rc;
   for (size_t i = 0; i < o.size(); ++i) out[i] = tnc_c128{o[i].real(), o[i].imag()};
   return TNC_OK;
