@@ -61,3 +61,19 @@ def test_many_batches_and_options():
         assert per < H.TOL_C64, (options, per, l2)
         whole = got if whole is None else whole
         assert np.abs(got - whole).max() <= 1e-13 * np.abs(whole).max()
+
+
+@pytest.mark.parametrize("d", list(range(2, 25)))
+def test_same_updates_as_the_own_passes(d):
+    # the host emulation of the plan's own passes does the same FP32 updates in
+    # the same order, so only the FP64 join and late program differ (up to 2^12
+    # products: 2^12 x 2^-53, and amplitudes some 2^5 below the sum of the
+    # products' sizes: 1e-11).  One update rounded in another order moves an
+    # amplitude by some 2^-24 / 2^6.
+    n = 9
+    for k in sorted({0, min(3, d // 2)}):
+        c = H.mixed_circuit(n, d, 37 * d + k, dense=0.3)
+        bits = W.random_bitstrings(n, 3, W.rng_for(503, d, k))
+        plan, _, got = run(c, bits, k)
+        ref = plan.debug_emulate_device(bits, k)
+        assert np.abs(got - ref).max() <= 1e-11 * max(np.abs(ref).max(), 2.0 ** (-n / 2)), (d, k)
