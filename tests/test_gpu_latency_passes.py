@@ -84,3 +84,19 @@ def test_tiles_by_size(d, nb):
     assert (got - ref).abs().max().item() <= 1e-13 * ref.abs().max().item()
     per, _ = H.amp_errors(got.cpu().numpy(), oracle.amplitudes(c, bits.cpu().numpy(), k), n)
     assert per < H.TOL_C64, per
+
+
+@pytest.mark.parametrize("d,nb", [(48, 16), (50, 8), (52, 4), (52, 5), (54, 2), (56, 1)])
+def test_streaming_tiles(d, nb):
+    # tensors of 2 GiB in all, whose lines the passes mark as not to be kept, in
+    # tiles of 256 threads (2^24 to 2^26 entries) and of 512, against 32 entries
+    # per thread, where no pass does: the same bits up to the FP64 late phase
+    from paper_2608_13110_amd import Plan
+    n, k = 7, 1
+    c = H.mixed_circuit(n, d, 41 * d, dense=0.3)
+    bits = torch.from_numpy(W.random_bitstrings(n, nb, W.rng_for(509, d))).cuda()
+    print(f"  [gpu] n={n} d={d} k={k} batches={nb}", flush=True)
+    got = Plan.from_circuit(c).amplitudes(bits, k)
+    ref = Plan.from_circuit(c, dict(max_tile_bits=13, low_bits=4, reg_bits=5)).amplitudes(bits, k)
+    torch.cuda.synchronize()
+    assert (got - ref).abs().max().item() <= 1e-13 * ref.abs().max().item()
