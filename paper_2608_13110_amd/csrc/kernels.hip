@@ -210,12 +210,17 @@ __global__ __launch_bounds__(kBlock) void k_resolve_g(const Seg<ResolveArgs>* __
 // so the batch and everything read through it are wave-uniform; such
 // kernels also run the fused matrix-core phases.
 // NT: threads per block (256; 512 for one 2^(R+9)-entry tile per block).
-// Resident waves per SIMD the register allocation must allow: LDS admits
-// five 2^12-entry (32 KiB) single-tile blocks per CU, so 16-entry phases in
-// 256-thread blocks ask for five; fused phases keep two.
+// Resident waves per SIMD the register allocation must allow.  LDS admits five
+// 32 KiB blocks of small 16-entry tiles (T - R < 6) per CU, but five waves leave
+// 96 registers, and the updates' fused operations need 124: what went to scratch
+// cost more than the fifth wave gives.  ms of the passes over the five-slot window
+// of a call at w = 24 (59 qubits, k = 8, two batches), five / four / three waves:
+// 6.60 / 3.88 / 3.88 (4.74 before the operations were spelled out, with 24 bytes of
+// scratch at five), in FP16 at w = 23 (13 batches) 25.0 / 12.4 / 12.8 (20.3).
+// Fused phases keep two.
 template <int R, bool WU, int NT>
 constexpr int pass_waves_per_eu() {
-  return WU ? 2 : (R == 4 && NT == 256 ? 5 : 1);
+  return WU ? 2 : (R == 4 && NT == 256 ? 4 : 1);
 }
 
 // Blocks are dispatched round-robin over the 8 XCDs; each XCD takes a

@@ -51,3 +51,9 @@ def test_join_sums_stay_in_registers():
     late = {n: k for n, k in kernels().items() if "k_late_dot" in n}
     assert len(late) >= 16  # four tensor types, one to eight columns
     assert {n: k[".private_segment_fixed_size"] for n, k in late.items() if k[".private_segment_fixed_size"]} == {}
+
+
+def test_complex64_passes_stay_in_registers():
+    passes = {n: k for n, k in kernels().items() if re.search(r"k_pass(_g)?ILi\dELb[01]ELb[01]ELi\d+ELi0E", n)}
+    assert len(passes) >= 30  # 2 to 32 entries per thread, whole tiles and several per block
+    assert {n: k[".private_segment_fixed_size"] for n, k in passes.items() if k[".private_segment_fixed_size"]} == {}
