@@ -1235,7 +1235,14 @@ static void pick_late_dot(Launch* L) {
 template <typename TIn, int S>
 static long long pick_late(const LateArgs& a, Launch* L) {
   if (a.N >= 4 && a.K >= 16 && a.M >= 64) {
-    const int CT = a.N >= 64 ? 64 : a.N >= 32 ? 32 : 16;
+    // 32 columns of up to 2^14 rows in all (a block per CU at most) take the 64-column
+    // tile as well: its blocks have half the rows, and the chain over K, which is all
+    // such a launch waits for, is shorter: 256 products, 2^12 rows 61 us against 80 in
+    // 128-row tiles, 2^14 rows 62 / 81; 32 products, 2^12 rows 12.1 / 13.6, 2^14 rows
+    // 14.7 / 14.7.  From 2^15 rows on the padding counts: 22.1 / 16.2.  (Either adds an
+    // output's products in the same order.)
+    const bool few = (long long)a.M * a.n_batches <= 1 << 14;
+    const int CT = a.N >= 64 || (a.N == 32 && few) ? 64 : a.N >= 32 ? 32 : 16;
     const int RT = CT == 64 ? 64 : 128;
     if (CT == 64) pick_late_mf<TIn, S, 64>(L);
     else if (CT == 32) pick_late_mf<TIn, S, 32>(L);

@@ -82,3 +82,23 @@ def test_folded_join(d, k, nb):
         assert (got - ref).abs().max().item() <= 1e-12 * ref.abs().max().item(), options
     per, _ = H.amp_errors(ref.cpu().numpy(), oracle.amplitudes(c, bits, k), n)
     assert per < H.TOL_C64, per
+
+
+@pytest.mark.parametrize("d,fold,nb", [(26, -1, 63), (26, -1, 64), (26, -1, 65), (26, -1, 300), (28, 2, 130), (33, 3, 65)])
+def test_groups_of_32_columns(d, fold, nb):
+    # 32 columns: few rows take other tiles than many, with the same bits, so a
+    # call does not depend on the groups its workspace splits it into
+    from paper_2608_13110_amd import Plan
+    n, k = 9, 5
+    c = H.mixed_circuit(n, d, 43 * d, dense=0.3)
+    bits = W.random_bitstrings(n, nb, W.rng_for(521, d, nb))
+    dev = torch.from_numpy(bits).cuda()
+    print(f"  [gpu] n={n} d={d} k={k} fold={fold} batches={nb}", flush=True)
+    plan = Plan.from_circuit(c, dict(late_fold=fold))
+    whole = plan.amplitudes(dev, k)
+    ws = torch.empty(plan.workspace_bytes(k, 7), dtype=torch.uint8, device="cuda")
+    groups = plan.amplitudes(dev, k, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(whole, groups)
+    per, l2 = H.amp_errors(whole.cpu().numpy(), oracle.amplitudes(c, bits, k), n)
+    assert per < H.TOL_C64 and l2 < H.TOL_C64, (per, l2)
