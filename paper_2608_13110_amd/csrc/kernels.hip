@@ -217,10 +217,13 @@ __global__ __launch_bounds__(kBlock) void k_resolve_g(const Seg<ResolveArgs>* __
 // of a call at w = 24 (59 qubits, k = 8, two batches), five / four / three waves:
 // 6.60 / 3.88 / 3.88 (4.74 before the operations were spelled out, with 24 bytes of
 // scratch at five), in FP16 at w = 23 (13 batches) 25.0 / 12.4 / 12.8 (20.3).
-// Fused phases keep two.
-template <int R, bool WU, int NT>
+// Eight-entry complex64 tiles of that kind took 64 registers and eight waves before
+// and 75 and six with the fused operations: asked for seven waves they take 72 and no
+// scratch (passes of a call at w = 19, 9 batches, 2^7-entry tiles: 1.31 ms, 1.46
+// and 1.37; eight waves 1.82, with scratch).  Fused phases keep two.
+template <int R, bool WU, int NT, bool C64>
 constexpr int pass_waves_per_eu() {
-  return WU ? 2 : (R == 4 && NT == 256 ? 4 : 1);
+  return WU ? 2 : NT != 256 ? 1 : R == 4 ? 4 : R == 3 && C64 ? 7 : 1;
 }
 
 // Blocks are dispatched round-robin over the 8 XCDs; each XCD takes a
@@ -344,14 +347,14 @@ __device__ __attribute__((always_inline)) inline void pass_body(const PassArgs& 
 // KIND 0: the bond-two phase forms (staircases, DUP, fused); KIND 1: the
 // bond-four ones (dense phases and single uncontrolled updates).
 template <int R, bool MULTI, bool WU, int NT = kBlock, int KIND = 0, bool Stream = false>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(pass_waves_per_eu<R, WU, NT>()))) void k_pass(
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(pass_waves_per_eu<R, WU, NT, KIND == 0>()))) void k_pass(
     PassArgs a) {
   extern __shared__ float2 lds[];
   pass_body<R, MULTI, WU, NT, KIND, Stream>(a, lds, blockIdx.x, gridDim.x);
 }
 
 template <int R, bool MULTI, bool WU, int NT = kBlock, int KIND = 0>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(pass_waves_per_eu<R, WU, NT>()))) void k_pass_g(
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(pass_waves_per_eu<R, WU, NT, KIND == 0>()))) void k_pass_g(
     const Seg<PassArgs>* __restrict__ segs) {
   extern __shared__ float2 lds[];
   const Seg<PassArgs>* s = group_seg(segs);
@@ -368,7 +371,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(pass_waves_p
 // after the pass).  4 entries (16 bytes) per HBM access, 2 when a thread
 // holds only 2 entries.
 template <int R, bool MULTI, int S, bool WU, int NT = kBlock, int KIND = 0>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(pass_waves_per_eu<R, WU, NT>()))) void k_pass16(
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(pass_waves_per_eu<R, WU, NT, false>()))) void k_pass16(
     PassArgs a) {
   extern __shared__ float2 lds[];
   constexpr int E = 1 << R;

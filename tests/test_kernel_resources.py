@@ -57,3 +57,6 @@ def test_complex64_passes_stay_in_registers():
     passes = {n: k for n, k in kernels().items() if re.search(r"k_pass(_g)?ILi\dELb[01]ELb[01]ELi\d+ELi0E", n)}
     assert len(passes) >= 30  # 2 to 32 entries per thread, whole tiles and several per block
     assert {n: k[".private_segment_fixed_size"] for n, k in passes.items() if k[".private_segment_fixed_size"]} == {}
+    # eight entries per thread, several tiles per block: seven waves per SIMD (512 / 7 registers)
+    small = {n: k[".vgpr_count"] for n, k in passes.items() if re.search(r"ILi3ELb1ELb0E", n)}
+    assert small and max(small.values()) <= 72, small
