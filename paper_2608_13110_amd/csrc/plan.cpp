@@ -7,8 +7,11 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <map>
 #include <set>
 #include <sstream>
+#include <tuple>
+#include <utility>
 
 namespace tnc {
 
@@ -797,6 +800,13 @@ bool fusable_start(const std::vector<SweepOp>& ops, int i, int end) {
   return true;
 }
 
+// The register and thread bits of staircase phases already laid out, by tile bits,
+// register bits, targets and op 0's control: every row of a sweep asks for the same
+// few, and a search over the padding registers takes some microseconds (a plan of
+// 60 qubits and 24 layers: 228 phases).
+using PhaseBits = std::pair<std::vector<int>, std::vector<int>>;
+using PhaseMemo = std::map<std::tuple<int, int, std::vector<int>, int>, PhaseBits>;
+
 // Register phases in canonical staircase form: op b of a phase targets
 // register bit b and, for b >= 1, is controlled by register bit b-1; op 0 is
 // either a DUP or an update whose control is not a register bit (or absent).
@@ -805,7 +815,7 @@ bool fusable_start(const std::vector<SweepOp>& ops, int i, int end) {
 // fuse keeps two of its targets in lane bits, so its staircase may run two
 // updates past the register bits (one when op 0's control takes the top
 // register bit).
-void plan_phases(Pass& ps, const std::vector<SweepOp>& ops, int R, bool fuse) {
+void plan_phases(Pass& ps, const std::vector<SweepOp>& ops, int R, bool fuse, PhaseMemo* memo) {
   const int T = ps.w.tile_bits();
   const int Reff = pass_reg_bits(R, T);
   fuse = fuse && Reff >= 3 && T - Reff >= 6 && T - Reff <= kMaxThreadBits;
@@ -923,12 +933,17 @@ void plan_phases(Pass& ps, const std::vector<SweepOp>& ops, int R, bool fuse) {
       regs.push_back(t);
     }
     ph.op_end = j;
-    pad_regs_lds(regs, ctl0, T, Reff);
-    for (int q = 0; q < kMaxReg; ++q) ph.reg[q] = q < int(regs.size()) ? regs[q] : -1;
-    std::vector<int> free_bits;
-    for (int c = 0; c < T; ++c)
-      if (std::find(regs.begin(), regs.end(), c) == regs.end()) free_bits.push_back(c);
-    const std::vector<int> lanes = lane_order(free_bits, -1, -1);
+    const auto found = memo->emplace(std::make_tuple(T, Reff, regs, ctl0), PhaseBits());
+    PhaseBits& bits = found.first->second;
+    if (found.second) {
+      pad_regs_lds(regs, ctl0, T, Reff);
+      std::vector<int> free_bits;
+      for (int c = 0; c < T; ++c)
+        if (std::find(regs.begin(), regs.end(), c) == regs.end()) free_bits.push_back(c);
+      bits = PhaseBits(regs, lane_order(free_bits, -1, -1));
+    }
+    const auto& [laid, lanes] = bits;
+    for (int q = 0; q < kMaxReg; ++q) ph.reg[q] = q < int(laid.size()) ? laid[q] : -1;
     for (int t = 0; t < kMaxThreadBits; ++t) ph.tpos[t] = t < int(lanes.size()) ? lanes[t] : -1;
     ps.phases.push_back(ph);
     i = j;
@@ -992,6 +1007,7 @@ void split_triples(Pass& ps, const std::vector<SweepOp>& ops) {
 std::vector<Pass> plan_passes(const Plan& p, const Options& opt, const std::vector<SweepOp>& ops, int R) {
   std::vector<Pass> passes;
   if (ops.empty()) return passes;
+  PhaseMemo memo;
   auto ws = p.chi == 4 && !p.spatial ? window_grid_overlap(p, p.h, 2) : window_grid(opt, p.h);
   int i = 0;
   const int nops = int(ops.size());
@@ -1009,7 +1025,7 @@ std::vector<Pass> plan_passes(const Plan& p, const Options& opt, const std::vect
     ps.op_end = i + best_len;
     const int T = ps.w.tile_bits();
     ps.R = pass_reg_bits(R, T);
-    plan_phases(ps, ops, ps.R, opt.math == 2);
+    plan_phases(ps, ops, ps.R, opt.math == 2, &memo);
     // Fewer entries per thread leave registers for more resident waves:
     // take one register bit less when the pass needs no more phases with
     // it and a tile still fits one 256-thread block.
@@ -1017,7 +1033,7 @@ std::vector<Pass> plan_passes(const Plan& p, const Options& opt, const std::vect
       Pass alt = ps;
       alt.R = ps.R - 1;
       alt.phases.clear();
-      plan_phases(alt, ops, alt.R, opt.math == 2);
+      plan_phases(alt, ops, alt.R, opt.math == 2, &memo);
       if (alt.phases.size() == ps.phases.size()) ps = alt;
     }
     if (opt.math == 2) split_triples(ps, ops);
@@ -1265,7 +1281,8 @@ Pass plan_one_tile(const Plan& p, const Schedule& s, int R) {
   ps.w.win_len = p.h;
   ps.op_end = int(s.ops.size());
   ps.R = pass_reg_bits(R, p.h);
-  plan_phases(ps, s.ops, ps.R, false);
+  PhaseMemo memo;
+  plan_phases(ps, s.ops, ps.R, false, &memo);
   return ps;
 }
 
