@@ -77,7 +77,13 @@ typedef struct {
   tnc_c128 m[16];
 } tnc_gate2;
 
-/* Tiling options of the pass kernels; zero fields take the defaults. */
+/* Tiling options of the pass kernels; zero fields take the defaults.  With
+ * max_tile_bits, reg_bits, low_bits, math and reg_adapt all zero, complex64 calls
+ * take their tiles by the tensor's size instead of these defaults (bond two, above
+ * 2^12 entries).  Complex64 calls of bond-two plans with at most 12 boundary bits,
+ * and at most 18 with the open legs, run as one launch whatever the tile options,
+ * unless math = 2 fuses a phase.  The updates and their order are the same on
+ * every route, so their results are as well. */
 typedef struct {
   int32_t max_tile_bits; /* entries per pass tile = 2^max_tile_bits (default 13, 6..14) */
   int32_t reg_bits;      /* entries per thread = 2^reg_bits (default 5, 1..5); at most 512
@@ -91,8 +97,10 @@ typedef struct {
                             reg_bits + 2 updates.  Other values: TNC_E_INVALID */
   int32_t late_fold;     /* k >= 1: late removals folded into the join launch (0:
                             automatic, 7 for boundary tensors of 2^35 entries, 5 for
-                            2^30 or more, 3 for 2^26 or more or for calls of 2^24
-                            entries together, else none; -1: none; 1..8: that many) */
+                            2^30 or more, 3 for 2^26 or more, else none; with k <= 8
+                            and tensors above 2^12 entries, calls of 2^24 entries
+                            together take 3 where that leaves the join 64 rows;
+                            -1: none; 1..8: that many) */
   int32_t reg_adapt;     /* 1: a pass takes reg_bits - 1 when that needs no more register
                             phases and its tile fits 256 threads (more resident waves);
                             0: every pass uses reg_bits (default) */
@@ -115,9 +123,10 @@ typedef struct {
   int32_t boundary_bits;      /* h = max crossings of a cut: device tensor has 2^h entries */
   int32_t live_slots_fixed;   /* legs of the boundary tensor after the fixed rows */
   int32_t n_ops;              /* boundary updates in the fixed sweep */
-  int32_t n_passes;           /* HBM passes of the fixed sweep */
-  int32_t n_phases;           /* register phases over all passes */
-  int32_t n_late_launches;    /* device launches of the late phase */
+  int32_t n_passes;           /* HBM passes of the fixed sweep, as tnc_plan_passes lists them */
+  int32_t n_phases;           /* register phases over those passes */
+  int32_t n_late_launches;    /* launches of the plan's own late phase (calls on other routes,
+                                 see tnc_options, make fewer) */
   int32_t fixed_rows;         /* rows contracted by the sweep (Alg. 2: q_1..q_{n-k}) */
   int32_t early_layers;       /* c = 2k entangling layers in the early region */
   int32_t late_layers;        /* d - c layers absorbed after the join */
@@ -263,7 +272,8 @@ int tnc_ring_info(tnc_ring_plan_t ring, int32_t k, int32_t n_batches, int32_t* n
 /* Ring amplitudes, with the arguments of tnc_amplitudes (complex64 storage):
  * the slices run in groups of up to 1024 on `stream` (the i-th launches of a
  * group's slices as one grouped launch), their results added to d_out in
- * slice order in FP64.  The workspace must hold what tnc_ring_info reports.
+ * FP64, in an order that n_batches and k fix.  The workspace must hold what
+ * tnc_ring_info reports.
  * The ring plan's pinned staging is reused call to call: one thread at a
  * time per ring plan. */
 int tnc_ring_amplitudes(tnc_ring_plan_t ring, int32_t n_batches, const uint8_t* d_bits, int32_t k, tnc_c128* d_out,
@@ -278,7 +288,8 @@ void tnc_ring_release(tnc_ring_plan_t ring);
  * Kernel timing with HIP events recorded on the launch stream around every
  * launch of tnc_amplitudes while profiling is on (process-wide).
  * tnc_profile_end waits for the recorded events and returns the summed
- * durations per kernel class (row-0 build-up, sweep passes, late phase).
+ * durations per kernel class (row-0 build-up, sweep passes, late phase).  A call
+ * that runs as one launch counts as a pass without bytes.
  */
 typedef struct {
   double init_ms;
@@ -306,7 +317,7 @@ int tnc_profile_launches(int32_t* cls, double* ms, int64_t cap, int64_t* n);
 int tnc_plan_passes(tnc_plan_t plan, int32_t k, int32_t* out, int32_t cap, int32_t* n_passes);
 
 /*
- * Tile autotuner.  Times each candidate tile option set on the current
+ * Tile autotuner.  Times calls with each candidate tile option set on the current
  * device for an n-qubit, d-layer brickwork CZ circuit with seeded random
  * one-qubit unitaries (width and pass structure depend only on n, d and k,
  * never on the gate values: the invariance of width and cost stated in Sec. 1 and Sec. 7) and
@@ -330,12 +341,13 @@ int tnc_autotune(int32_t n, int32_t d, int32_t k, int32_t storage, const tnc_opt
  * n_streams HIP streams is free and the device arena has room for its
  * footprint (workspace + bits + output), oldest first, letting younger
  * requests that fit pass an older one that does not at most 16 times.
- * Small requests (boundary tensor of <= small_bits bits) run together: the
- * ready complex64 requests of the admitted one's width (up to max_group)
- * form a group whose launches are merged, launch by launch, into grouped
- * launches of one kernel each (one segment per member).  A small request
- * whose (plan, k, batches, storage) has been served before runs as a cached
- * HIP graph, built node by node from its launches (never by stream capture),
+ * Small requests (boundary tensor of <= small_bits bits) run together where
+ * they would otherwise wait (more are ready than streams are free, or a
+ * group_window_us is set): the ready complex64 requests of the admitted one's
+ * width (up to max_group) form a group whose launches are merged, launch by
+ * launch, into grouped launches of one kernel each (one segment per member).  A
+ * small request whose (plan, k, batches, storage) has been served before runs as a
+ * cached HIP graph, built node by node from its launches (never by stream capture),
  * which owns its device region (within a quarter of the arena) and is
  * replayed, from any stream, while idle.  No stream is ever put in capture
  * mode, so other threads may use the device freely meanwhile.

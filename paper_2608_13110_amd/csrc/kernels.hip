@@ -615,7 +615,8 @@ static hipError_t record_pass_r(const PassArgs& a, Launch* L) {
     if (s16) pick_pass16<R, kBlock, true, false>(L, a.store, a.kind);
     else pick_pass<R, kBlock, true, false>(L, a.kind);
   }
-  // streaming tensors (whole tiles per block)
+  // streaming tensors (whole tiles per block of 16 entries per thread: the tiles
+  // that large calls take by size, and the option sets that the tuner picks for them)
   const bool runs = a.lo_bits == 0 || (sizeof(float2) << a.lo_bits) >= 128;
   if constexpr (R == 4) {
     if (!s16 && !multi && runs && ((uint64_t)a.n_tiles << (a.T + 3)) >= kStreamBytes) {
