@@ -953,9 +953,9 @@ __device__ inline double2 late_in(const LateArgs& a, const TIn* __restrict__ in,
 // other (lane_reduce), the KS waves' sums meet in LDS.  Bound by the read of
 // the tensor.  A 64 x 64-tile kernel took 64 columns of arithmetic for these
 // one to eight: 282 us for one amplitude at w = 10 and 1582 us for the 2^25
-// entries of a bond-four circuit of 26 layers (256 MiB), against 7 us and 121 us
-// (2.2 TB/s) here.  Conditional loads of the rows past M made the compiler wait
-// on each (177 us).
+// entries of a bond-four circuit of 26 layers (256 MiB, two columns), against 7 us
+// and 55 us (4.9 TB/s) here.  Conditional loads of the rows past M made the
+// compiler wait on each (121 -> 177 us, measured with the sums in scratch).
 // (one function per halving, so that every index is a constant: as a loop over h
 // it was not unrolled at V = 32, and the sums went to scratch memory)
 template <int H, int Mask, int V>
